@@ -7,14 +7,19 @@
  *
  *   z^(l1,l2,l3)_m3 = sum_{m1,m2} C^{l3 m3}_{l1 m1 l2 m2} x1^(l1)_m1 x2^(l2)_m2
  *
- * (the CGTP of Section 1 and Appendix F.1), the paper's way: each (l1, l2)
- * block is one irrep-signal tensor product (Section 4.3).  Both inputs are
+ * (the CGTP of Section 1 and Appendix F.1), by one of two routes with the same
+ * result up to rounding.  A plan with a grid or cover of the caller's choice
+ * goes the paper's way: each (l1, l2) block is one irrep-signal tensor product
+ * (Section 4.3).  Both inputs are
  * lifted to scalar and toroidal vector signals on a sphere grid (tensor
  * spherical harmonics, Definition 4.1), multiplied pointwise (scalar-scalar
  * product and cross product, Section 5.1, or scalar-vector and dot product
  * for the alternate cover), transformed back, and each path is divided by the
  * factor the generalized Gaunt formula (Theorem 4.2) fixes.  Corollary 5.3 is
- * what makes one such product per block enough.
+ * what makes one such product per block enough.  A plan that leaves both open
+ * (n_theta = n_phi = 0, default cover) contracts the coefficients directly on
+ * the matrix cores, order by order: up to L = 32 that is the faster route, a
+ * fifth of the arithmetic and bound by writing the outputs.
  *
  * Conventions: complex spherical basis with Condon-Shortley phase
  * (quantum-mechanics conventions, footnote of Section 3.3); coefficients are

@@ -1,0 +1,112 @@
+// Internal layout of the direct contraction, shared by its plan
+// (cgtp_direct_plan.cpp) and its kernels (cgtp_direct.hip).  Not part of the
+// public ABI.
+//
+// Every (l1, l2) block of the CGTP is, per order M >= 0 of the output, one
+// square orthogonal matrix of Clebsch-Gordan coefficients
+//   A_M[l3][k] = C^{l3 M}_{la ma, lb M-ma},  ma = la - k,
+// (la <= lb the block's degrees, n(M) = min(2 la + 1, la + lb - M + 1) rows and
+// columns) applied to the products x_a[ma] x_b[M - ma] of every pair; orders
+// -M use the same matrix on the reversed products, up to the sign
+// (-1)^(l1+l2-l3), and block (lb, la) the same up to that sign.  Per block that
+// is 2 n^2 multiply-adds per M for 2 n outputs: at L = 32 31 M per pair, a
+// fifth of the arithmetic of the sphere-grid method, all of it on the matrix
+// cores, and the outputs are then bound by the memory they are written to.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+#include <cstdint>
+
+namespace cgtp {
+
+// A wave works on 64 columns at once: kDirPairs pairs x 2 (orders +M and -M;
+// real basis: real and imaginary part) x G groups of four consecutive orders.
+// fp32: G = 2 groups on v_mfma_f32_4x4x1_16b (16 blocks of 4 rows x 4 columns;
+// the coefficients of 8 k steps x 4 rows of each group fill one operand
+// register, and the instruction broadcasts the step's block to its group).
+// fp64: G = 1, vector multiply-adds with the coefficient in scalar registers.
+template <typename T> struct DirGeom;
+template <> struct DirGeom<float> {
+    static constexpr int G = 2;
+};
+template <> struct DirGeom<double> {
+    static constexpr int G = 1;
+};
+template <typename T> __host__ __device__ constexpr int dir_pairs() { return 32 / DirGeom<T>::G; }
+template <typename T> __host__ __device__ constexpr int dir_kc() { return 16 / DirGeom<T>::G; }       // k steps per coefficient chunk
+template <typename T> __host__ __device__ constexpr int dir_orders() { return 4 * DirGeom<T>::G; }    // orders M per item
+constexpr int kDirThreads = 512;
+constexpr int kDirWaves = kDirThreads / 64;
+constexpr int kDirRows = 4;        // output degrees l3 per item
+constexpr int kDirChunk = 256;     // coefficients per chunk
+
+// LDS tile of one input: per degree l, 2 l + 1 rows (order m = row - l) and
+// dir_orders - 1 zero rows, which the last orders of an item read past the
+// degree; a row holds the 2 dir_pairs columns and one element of padding.
+template <typename T> __host__ __device__ constexpr int dir_row() { return 2 * dir_pairs<T>() + 1; }
+template <typename T> __host__ __device__ constexpr int dir_pad() { return dir_orders<T>() - 1; }
+template <typename T> __host__ __device__ inline int dir_tile_row(int l, int l0) {
+    return l * l - l0 * l0 + dir_pad<T>() * (l - l0);
+}
+
+// One item: 4 output degrees lt, lt-1, lt-2, lt-3 (those >= lmin) of one block
+// for the orders m0 .. m0 + dir_orders - 1 (those <= the degree).
+struct alignas(16) DirItem {
+    int32_t chunk0;   // first coefficient chunk
+    int32_t nk;       // k steps: n(m0)
+    int32_t xa;       // tile element of (la, ma = la); step k is k rows further down
+    int32_t xb;       // tile element of (lb, mb = m0 - la); step k is k rows further up
+    int32_t code;     // lt | lmin << 8 | m0 << 16 | (l1 > l2) << 24
+    int32_t c;        // output (l3, M) sits at c + l3^2 + l3 + M of the stage's run
+    int32_t path;     // path (l1, l2, l3) has index path + l3
+    int32_t pad;
+};
+
+// One stage: a run of consecutive outputs of every pair, small enough to be
+// put together in LDS and written as whole lines.
+struct DirStage {
+    int32_t item0, nitems;   // heaviest items first
+    int32_t off, len;        // run of one pair's output
+};
+
+// One group: the consecutive stages a work-group makes from one filling of the
+// input tiles (x1 degrees l1a..l1b, x2 degrees l2a..l2b).
+struct DirGroup {
+    int32_t stage0, nstages;
+    int32_t l1a, l1b, l2a, l2b;
+    int32_t x2tile;      // first element of the x2 tile (x1's is at 0)
+    int32_t tile_len;    // elements of both tiles, a multiple of 4
+};
+
+template <typename T>
+struct DirTables {
+    const T* coef;
+    const DirItem* items;
+    const DirStage* stages;
+    const DirGroup* groups;
+    int32_t ngroups;
+    int32_t lds_bytes;
+};
+
+// fp32 coefficients of a chunk: element (lane, mi) at 4 lane + mi with
+// lane = ((group of orders) kc + k) 4 + row; fp64: (k, mi, row) at 16 k + 4 mi + row.
+template <typename T> __host__ __device__ inline int dir_coef_index(int k, int order, int row);
+template <> __host__ __device__ inline int dir_coef_index<float>(int k, int order, int row) {
+    return (((order >> 2) * dir_kc<float>() + k) * 4 + row) * 4 + (order & 3);
+}
+template <> __host__ __device__ inline int dir_coef_index<double>(int k, int order, int row) {
+    return 16 * k + 4 * order + row;
+}
+
+template <typename T> struct ChanArgs;
+
+// Weak, so that the plan's host code also links without the device code (it
+// never calls them then: no table can be uploaded).
+__attribute__((weak)) int launch_direct_f32(const DirTables<float>& tb, const float* x1, const float* x2, float* out, int64_t N, int L,
+                      const ChanArgs<float>* ch, bool real_basis, void* stream);
+__attribute__((weak)) int launch_direct_f64(const DirTables<double>& tb, const double* x1, const double* x2, double* out, int64_t N, int L,
+                      const ChanArgs<double>* ch, bool real_basis, void* stream);
+
+}  // namespace cgtp

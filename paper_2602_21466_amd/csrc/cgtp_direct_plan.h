@@ -1,0 +1,212 @@
+// Plan of the direct contraction (host): the Clebsch-Gordan matrices of every
+// block and the lists of items, stages and groups (cgtp_direct.h).
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <map>
+#include <utility>
+#include <vector>
+
+#include "cgtp_direct.h"
+
+namespace cgtp {
+
+template <typename T>
+struct DirHost {
+    std::vector<T> coef;
+    std::vector<DirItem> items;
+    std::vector<DirStage> stages;
+    std::vector<DirGroup> groups;
+    int lds_bytes = 0;
+};
+
+// For fixed (la, lb, M) the coefficients of l3 are the eigenvector of
+// J^2 = (Ja + Jb)^2 with eigenvalue l3 (l3 + 1) in the basis |ma, M - ma>, where
+// J^2 is tridiagonal: diagonal la (la+1) + lb (lb+1) + 2 ma mb, off-diagonal
+// sqrt((la - ma)(la + ma + 1)) sqrt((lb + mb)(lb - mb + 1)) between ma and ma + 1.
+// The three-term recurrence is run from both ends, where it grows, and joined
+// at the first maximum seen from the upper end, so neither run enters a region
+// in which it would amplify rounding.  Signs: the coefficient at the largest
+// ma (ma = la, or mb = -lb) is positive in the Condon-Shortley convention (it
+// is a single positive term of the Racah sum).
+// out[M][r n + k] = C^{l3 M}_{la ma, lb M-ma}, l3 = la + lb - r, ma = la - k,
+// n = min(2 la + 1, la + lb - M + 1).
+inline void dir_cg_block(int la, int lb, std::vector<std::vector<double>>& out) {
+    out.assign((size_t)(la + lb + 1), {});
+    std::vector<double> dg, of, up, dn;
+    for (int M = 0; M <= la + lb; ++M) {
+        const int n = std::min(2 * la + 1, la + lb - M + 1);
+        auto& o = out[(size_t)M];
+        o.assign((size_t)n * n, 0.0);
+        dg.assign(n, 0.0);
+        of.assign(n, 0.0);   // of[k]: between k and k + 1
+        for (int k = 0; k < n; ++k) {
+            const int ma = la - k, mb = M - ma;
+            dg[k] = (double)(la * (la + 1) + lb * (lb + 1) + 2 * ma * mb);
+            // ma -> ma - 1, mb -> mb + 1
+            of[k] = std::sqrt((double)(la + ma) * (la - ma + 1) * (double)(lb - mb) * (lb + mb + 1));
+        }
+        up.assign(n, 0.0);
+        dn.assign(n, 0.0);
+        for (int r = 0; r < n; ++r) {
+            const int l3 = la + lb - r;
+            const double ev = (double)l3 * (l3 + 1);
+            up[0] = 1.0;
+            int join = n - 1;
+            for (int k = 0; k + 1 < n; ++k) {
+                up[k + 1] = ((ev - dg[k]) * up[k] - (k ? of[k - 1] * up[k - 1] : 0.0)) / of[k];
+                if (std::fabs(up[k + 1]) < std::fabs(up[k])) {
+                    join = k;
+                    break;
+                }
+            }
+            dn[n - 1] = 1.0;
+            for (int k = n - 1; k > join; --k)
+                dn[k - 1] = ((ev - dg[k]) * dn[k] - (k + 1 < n ? of[k] * dn[k + 1] : 0.0)) / of[k - 1];
+            const double s = up[join] / dn[join];
+            double norm = 0;
+            for (int k = 0; k < n; ++k) {
+                const double v = k <= join ? up[k] : s * dn[k];
+                o[(size_t)r * n + k] = v;
+                norm += v * v;
+            }
+            const double f = 1.0 / std::sqrt(norm);
+            for (int k = 0; k < n; ++k) o[(size_t)r * n + k] *= f;
+        }
+    }
+}
+
+// The coefficient table and the work lists of degree L.
+template <typename T>
+void dir_build(int L, DirHost<T>& h) {
+    constexpr int P = dir_pairs<T>(), KC = dir_kc<T>(), HM = dir_orders<T>();
+    // a stage's run, per pair: up to 40 KiB (fp32) of LDS for the pairs of a
+    // work-group, so that two work-groups share a CU; four degrees of the
+    // largest block always fit
+    const int max_len = std::max(40 * 1024 / (P * 4) - 1, 8 * L - 8);
+    // a group takes blocks together until one filling of the input tiles serves
+    // about two stages' worth of outputs, with tiles of at most 24 KiB (fp32)
+    const int group_len = 2 * max_len, max_tile = sizeof(T) == 4 ? 6144 : 7680;
+
+    // coefficients of the blocks la <= lb: first chunk of (row group, orders m0..)
+    std::map<std::pair<int, int>, std::vector<std::vector<int>>> first;
+    std::vector<std::vector<double>> cg;
+    for (int la = 0; la <= L; ++la)
+        for (int lb = la; lb <= L; ++lb) {
+            dir_cg_block(la, lb, cg);
+            auto& f = first[{la, lb}];
+            f.resize((size_t)(2 * la + 1 + kDirRows - 1) / kDirRows);
+            for (int rg = 0; rg < (int)f.size(); ++rg) {
+                const int lt = la + lb - kDirRows * rg;
+                for (int m0 = 0; m0 <= lt; m0 += HM) {
+                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
+                    const int nch = (nk + KC - 1) / KC;
+                    const size_t at = h.coef.size();
+                    f[(size_t)rg].push_back((int)(at / kDirChunk));
+                    h.coef.resize(at + (size_t)nch * kDirChunk, (T)0);
+                    for (int o = 0; o < HM && m0 + o <= lt; ++o) {
+                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
+                        const auto& a = cg[(size_t)(m0 + o)];
+                        for (int r = 0; r < kDirRows && kDirRows * rg + r < n; ++r)
+                            for (int k = 0; k < n; ++k)
+                                h.coef[at + (size_t)(k / KC) * kDirChunk + dir_coef_index<T>(k % KC, o, r)] =
+                                    (T)a[(size_t)(kDirRows * rg + r) * n + k];
+                    }
+                }
+            }
+        }
+
+    struct Piece {   // one row group of one block, in output order
+        int l1, l2, rg, off, len;
+    };
+    struct Cost {
+        DirGroup g;
+        int64_t cost;
+    };
+    std::vector<Cost> groups;
+    const int nblk = (L + 1) * (L + 1);
+    int off = 0, path = 0;
+    std::vector<int> boff(nblk), bpath(nblk);
+    for (int b = 0; b < nblk; ++b) {
+        const int l1 = b / (L + 1), l2 = b % (L + 1);
+        boff[b] = off;
+        bpath[b] = path;
+        off += (2 * l1 + 1) * (2 * l2 + 1);
+        path += 2 * std::min(l1, l2) + 1;
+    }
+    size_t lds = 0;
+    for (int b0 = 0; b0 < nblk;) {
+        // blocks b0 .. b1-1 of the group
+        DirGroup g{};
+        int b1 = b0, outs = 0;
+        g.l1a = g.l1b = b0 / (L + 1);
+        g.l2a = g.l2b = b0 % (L + 1);
+        while (b1 < nblk) {
+            const int l1 = b1 / (L + 1), l2 = b1 % (L + 1);
+            const int sz = (2 * l1 + 1) * (2 * l2 + 1);
+            const int l1b = std::max(g.l1b, l1), l2a = std::min(g.l2a, l2), l2b = std::max(g.l2b, l2);
+            const int rows = dir_tile_row<T>(l1b + 1, g.l1a) + dir_tile_row<T>(l2b + 1, l2a);
+            if (b1 > b0 && (outs + sz > group_len || rows * dir_row<T>() > max_tile)) break;
+            outs += sz;
+            g.l1b = l1b;
+            g.l2a = l2a;
+            g.l2b = l2b;
+            ++b1;
+        }
+        const int rows1 = dir_tile_row<T>(g.l1b + 1, g.l1a), rows2 = dir_tile_row<T>(g.l2b + 1, g.l2a);
+        g.x2tile = rows1 * dir_row<T>();
+        g.tile_len = ((rows1 + rows2) * dir_row<T>() + 3) & ~3;
+        g.stage0 = (int)h.stages.size();
+        std::vector<Piece> pieces;
+        for (int b = b0; b < b1; ++b) {
+            const int l1 = b / (L + 1), l2 = b % (L + 1), la = std::min(l1, l2), d = std::abs(l1 - l2);
+            for (int rg = (2 * la + kDirRows) / kDirRows - 1; rg >= 0; --rg) {
+                const int hi = l1 + l2 - kDirRows * rg, lo = std::max(d, hi - kDirRows + 1);
+                pieces.push_back({l1, l2, rg, boff[b] + lo * lo - d * d, (hi + 1) * (hi + 1) - lo * lo});
+            }
+        }
+        int64_t cost = 0;
+        for (size_t i = 0; i < pieces.size();) {
+            DirStage st{(int)h.items.size(), 0, pieces[i].off, 0};
+            size_t j = i;
+            for (; j < pieces.size() && (j == i || st.len + pieces[j].len <= max_len); ++j) {
+                const Piece& q = pieces[j];
+                st.len += q.len;
+                const int la = std::min(q.l1, q.l2), lb = std::max(q.l1, q.l2), d = lb - la;
+                const bool swap = q.l1 > q.l2;
+                const int b = q.l1 * (L + 1) + q.l2, lt = q.l1 + q.l2 - kDirRows * q.rg;
+                const int t1 = dir_tile_row<T>(q.l1, g.l1a) * dir_row<T>();
+                const int t2 = g.x2tile + dir_tile_row<T>(q.l2, g.l2a) * dir_row<T>();
+                const auto& f = first[{la, lb}][(size_t)q.rg];
+                for (int m0 = 0; m0 <= lt; m0 += HM) {
+                    DirItem it{};
+                    it.chunk0 = f[(size_t)(m0 / HM)];
+                    it.nk = std::min(2 * la + 1, la + lb - m0 + 1);
+                    it.xa = (swap ? t2 : t1) + 2 * la * dir_row<T>();
+                    it.xb = (swap ? t1 : t2) + (lb + m0 - la) * dir_row<T>();
+                    it.code = lt | d << 8 | m0 << 16 | (swap ? 1 << 24 : 0);
+                    it.c = boff[b] - d * d - st.off;
+                    it.path = bpath[b] - d;
+                    h.items.push_back(it);
+                    cost += it.nk + 6;
+                }
+            }
+            st.nitems = (int)h.items.size() - st.item0;
+            std::stable_sort(h.items.begin() + st.item0, h.items.end(),
+                             [](const DirItem& x, const DirItem& y) { return x.nk > y.nk; });
+            lds = std::max(lds, ((size_t)g.tile_len + (size_t)P * (st.len | 1)) * sizeof(T));
+            h.stages.push_back(st);
+            i = j;
+        }
+        g.nstages = (int)h.stages.size() - g.stage0;
+        groups.push_back({g, cost});
+        b0 = b1;
+    }
+    std::stable_sort(groups.begin(), groups.end(), [](const Cost& x, const Cost& y) { return x.cost > y.cost; });
+    for (const auto& c : groups) h.groups.push_back(c.g);
+    h.lds_bytes = (int)lds;
+}
+
+}  // namespace cgtp

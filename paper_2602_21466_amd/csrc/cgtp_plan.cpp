@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../../include/cgtp.h"
+#include "cgtp_direct_plan.h"
 #include "cgtp_internal.h"
 
 using cgtp::BlockDesc;
@@ -361,6 +362,12 @@ struct cgtp_plan_s {
     double min_abs_K = 0, flops_per_pair = 0, bytes_per_pair = 0;
     double bwd_flops_per_pair = 0;
     double cross_cg = 0, dot_cg = 0;
+    // plans without a grid or cover of the caller's choice run the direct
+    // contraction: the same outputs, bound by writing them, at every degree
+    bool direct = false;
+    void* dmem_dir = nullptr;
+    cgtp::DirTables<float> df{};
+    cgtp::DirTables<double> dd{};
 };
 
 namespace {
@@ -876,6 +883,41 @@ int upload(cgtp_plan_s* p, const std::vector<BlockDesc>& blocks, const HostTable
     return CGTP_OK;
 }
 
+template <typename T>
+int upload_direct(cgtp_plan_s* p, cgtp::DirTables<T>* tb) {
+    cgtp::DirHost<T> h;
+    cgtp::dir_build<T>(p->L, h);
+    const size_t n[4] = {h.coef.size() * sizeof(T), h.items.size() * sizeof(cgtp::DirItem),
+                         h.stages.size() * sizeof(cgtp::DirStage), h.groups.size() * sizeof(cgtp::DirGroup)};
+    const void* src[4] = {h.coef.data(), h.items.data(), h.stages.data(), h.groups.data()};
+    size_t offs[4], total = 0;
+    for (int i = 0; i < 4; ++i) {
+        offs[i] = total;
+        total = align_up(total + n[i], 256);
+    }
+    hipError_t e = hipMalloc(&p->dmem_dir, total);
+    if (e != hipSuccess) {
+        g_last_hip_error = (int)e;
+        p->dmem_dir = nullptr;
+        return e == hipErrorOutOfMemory ? CGTP_ENOMEM : CGTP_EHIP;
+    }
+    char* base = (char*)p->dmem_dir;
+    for (int i = 0; i < 4; ++i) {
+        e = hipMemcpy(base + offs[i], src[i], n[i], hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            g_last_hip_error = (int)e;
+            return CGTP_EHIP;
+        }
+    }
+    tb->coef = (const T*)(base + offs[0]);
+    tb->items = (const cgtp::DirItem*)(base + offs[1]);
+    tb->stages = (const cgtp::DirStage*)(base + offs[2]);
+    tb->groups = (const cgtp::DirGroup*)(base + offs[3]);
+    tb->ngroups = (int32_t)h.groups.size();
+    tb->lds_bytes = h.lds_bytes;
+    return CGTP_OK;
+}
+
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
     const char *pa = (const char*)a, *pb = (const char*)b;
     return pa < pb + nb && pb < pa + na;
@@ -998,8 +1040,11 @@ int cgtp_plan(int32_t L, const cgtp_grid* grid, cgtp_plan_t* plan_out) {
         rc = build<double>(p, blocks, h, list);
         if (rc == CGTP_OK) rc = upload<double>(p, blocks, h, list, &p->td);
     }
+    p->direct = g.n_theta == 0 && g.n_phi == 0 && g.cover == CGTP_COVER_DEFAULT;
+    if (rc == CGTP_OK && p->direct)
+        rc = g.dtype == CGTP_FP32 ? upload_direct<float>(p, &p->df) : upload_direct<double>(p, &p->dd);
     if (rc != CGTP_OK) {
-        delete p;
+        (void)cgtp_destroy(p);
         return rc;
     }
     *plan_out = p;
@@ -1011,6 +1056,10 @@ int cgtp_destroy(cgtp_plan_t plan) {
     int rc = CGTP_OK;
     if (plan->dmem) {
         hipError_t e = hipFree(plan->dmem);
+        if (e != hipSuccess) { g_last_hip_error = (int)e; rc = CGTP_EHIP; }
+    }
+    if (plan->dmem_dir) {
+        hipError_t e = hipFree(plan->dmem_dir);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = CGTP_EHIP; }
     }
     delete plan;
@@ -1056,6 +1105,24 @@ int forward_rows(cgtp_plan_t plan, const void* x1, const void* x2, const void* w
         return CGTP_EHIP;
     }
     if (dev != plan->device) return CGTP_EINVAL;
+    if (plan->direct) {
+        const bool rows = channels != 1 || flags != 0 || w;
+        int err;
+        if (plan->grid.dtype == CGTP_FP32) {
+            const cgtp::ChanArgs<float> ch{(const float*)w, channels, flags, (int32_t)npaths};
+            err = cgtp::launch_direct_f32(plan->df, (const float*)x1, (const float*)x2, (float*)out, N, L,
+                                          rows ? &ch : nullptr, real_basis, hip_stream);
+        } else {
+            const cgtp::ChanArgs<double> ch{(const double*)w, channels, flags, (int32_t)npaths};
+            err = cgtp::launch_direct_f64(plan->dd, (const double*)x1, (const double*)x2, (double*)out, N, L,
+                                          rows ? &ch : nullptr, real_basis, hip_stream);
+        }
+        if (err != 0) {
+            g_last_hip_error = err;
+            return CGTP_EHIP;
+        }
+        return CGTP_OK;
+    }
     cgtp::LaunchMap map{};
     map.ncls = (int32_t)plan->classes.size();
     map.cum[0] = 0;

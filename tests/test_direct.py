@@ -1,0 +1,121 @@
+"""The direct contraction (plans without a grid or cover of the caller's choice).
+
+CPU: the plan's work lists run by a host model (direct_model.cpp) that checks
+every index and compares with the oracle's coefficients.  GPU: parity with the
+fp64 oracle where tiles of pairs, chunks of k steps, row groups and stages end,
+and agreement with the sphere-grid route, which an explicit grid selects.
+
+Bounds: a sum of at most 65 products of 32-bit numbers with 32-bit
+coefficients is off by a few 2^-24 of its terms' norm; 1e-6 relative L2 per
+call (1e-14 in 64 bits) is about ten times that."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TOL = {"fp32": 1e-6, "fp64": 1e-14}
+
+
+@pytest.fixture(scope="module")
+def model(tmp_path_factory):
+    if shutil.which("g++") is None or shutil.which("gcc") is None:
+        pytest.skip("no host compiler")
+    out = tmp_path_factory.mktemp("direct")
+    obj, exe = str(out / "oracle.o"), str(out / "direct_model")
+    subprocess.run(["gcc", "-O2", "-std=c11", "-fopenmp", "-c", os.path.join(ROOT, "oracle", "cgtp_oracle.c"), "-o", obj],
+                   check=True)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "tests", "sanitize"), "-I", "/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2602_21466_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "direct_model.cpp"), obj, "-fopenmp", "-lm", "-o", exe], check=True)
+    return lambda *a: float(subprocess.run([exe] + [str(v) for v in a], check=True, capture_output=True,
+                                           text=True).stdout)
+
+
+def test_coefficients_match_the_racah_formula(model):
+    """Every 12th block (la <= lb) up to degree 32, every order and degree."""
+    assert model("cg", 32) < 5e-14
+
+
+@pytest.mark.parametrize("dtype,L", [("fp32", 0), ("fp32", 1), ("fp32", 2), ("fp32", 4), ("fp32", 7), ("fp32", 11),
+                                     ("fp32", 16), ("fp64", 0), ("fp64", 3), ("fp64", 8)])
+def test_work_lists_cover_every_output_once(model, dtype, L):
+    assert model(dtype, L) < TOL[dtype]
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def _rows(torch, n, cols, dtype, seed):
+    g = torch.Generator("cpu").manual_seed(seed)
+    return torch.randn(n, cols, dtype=torch.float64, generator=g).to({"fp32": torch.float32, "fp64": torch.float64}[dtype])
+
+
+# ragged tiles of 16 (fp32) and 32 (fp64) pairs; degrees whose blocks end inside and at the end of
+# row groups, chunks of 8 / 16 k steps, groups of 8 / 4 orders, and with one or several stages
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,N,dtype", [(0, 1, "fp32"), (1, 15, "fp32"), (2, 16, "fp32"), (3, 17, "fp32"), (5, 33, "fp32"),
+                                       (8, 3, "fp32"), (13, 18, "fp32"), (20, 2, "fp32"), (0, 33, "fp64"),
+                                       (2, 31, "fp64"), (4, 32, "fp64"), (9, 5, "fp64")])
+def test_forward_and_real_match_oracle(L, N, dtype):
+    import torch
+    import oracle
+    import paper_2602_21466_amd as lib
+    print("case L=%d N=%d %s" % (L, N, dtype), flush=True)
+    x1, x2 = _rows(torch, N, (L + 1) ** 2, dtype, L), _rows(torch, N, (L + 1) ** 2, dtype, 100 + L)
+    a, b = x1.double().numpy(), x2.double().numpy()
+    plan = lib.Plan(L, dtype=dtype)
+    z = plan.forward(x1.cuda(), x2.cuda()).double().cpu().numpy()
+    r = plan.forward_real(x1.cuda(), x2.cuda()).double().cpu().numpy()
+    assert _rel(z, oracle.cgtp(L, a, b)) < TOL[dtype]
+    assert _rel(r, oracle.cgtp_real(L, a, b)) < TOL[dtype]
+    plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shared,weights", [(True, "channel"), (False, "pair"), (True, "none")])
+def test_routes_agree(shared, weights):
+    """The direct contraction and the sphere-grid kernels (explicit grid): plain, real, channels (bound: the sum of
+    both routes' errors, the grid route's per-call error is below 1e-6 at this degree)."""
+    import torch
+    import cgtp_inputs
+    import paper_2602_21466_amd as lib
+    L, N, C = 6, 7, 5
+    x1, x2, w = cgtp_inputs.channel_inputs(L, N, C, shared, weights, "fp32", seed=3)
+    x1, x2, w = x1.cuda(), x2.cuda(), None if w is None else w.cuda()
+    direct, grid = lib.Plan(L), lib.Plan(L, n_theta=2 * L + 2, n_phi=27)
+    a, b = (p.forward_weighted(x1, x2, w).double().cpu().numpy() for p in (direct, grid))
+    assert _rel(a, b) < 2e-6
+    y1, y2 = x1.reshape(N * C, -1), x1.flip(0).reshape(N * C, -1).contiguous()
+    for name in ("forward", "forward_real"):
+        a, b = (getattr(p, name)(y1, y2).double().cpu().numpy() for p in (direct, grid))
+        assert _rel(a, b) < 2e-6
+    direct.close()
+    grid.close()
+
+
+@pytest.mark.gpu
+def test_infinite_input_stays_in_its_blocks():
+    """A degree holding an infinity spoils only the blocks that read it, and other pairs nothing at all."""
+    import torch
+    import paper_2602_21466_amd as lib
+    L, N = 5, 19
+    x1, x2 = _rows(torch, N, (L + 1) ** 2, "fp32", 1).cuda(), _rows(torch, N, (L + 1) ** 2, "fp32", 2).cuda()
+    plan = lib.Plan(L)
+    ref = plan.forward(x1, x2)
+    l, n = 3, 4
+    for which in (0, 1):
+        y = [x1.clone(), x2.clone()]
+        y[which][n, l * l + 2] = float("inf")
+        z = plan.forward(*y)
+        keep = torch.ones_like(z, dtype=torch.bool)
+        for k in range(L + 1):
+            l1, l2 = (l, k) if which == 0 else (k, l)
+            o = lib.cgtp_path_offset(L, l1, l2, abs(l1 - l2))
+            keep[n, o:o + (2 * l1 + 1) * (2 * l2 + 1)] = False
+        assert torch.equal(z[keep], ref[keep])
+    plan.close()
