@@ -161,7 +161,8 @@ int cgtp_forward_weighted(cgtp_plan_t plan, const void *x1, const void *x2, cons
  *   grad_x1[n, (l1, m1)] = sum over paths and m2, m3 of C^{l3 m3}_{l1 m1 l2 m2} x2[n, (l2, m2)] grad_out[n, (l1, l2, l3), m3]
  *   grad_x2[n, (l2, m2)] = sum over paths and m1, m3 of C^{l3 m3}_{l1 m1 l2 m2} x1[n, (l1, m1)] grad_out[n, (l1, l2, l3), m3]
  * (the CGTP is bilinear: each gradient is the transpose of a linear map).
- * Computed by the method of the forward call run backwards, block by block
+ * fp32 plans of the direct contraction apply its matrices transposed.  Other
+ * plans run the sphere-grid method backwards, block by block
  * (Section 4.3): the adjoint of every stage (recombination and 1/K, Legendre
  * projection, longitude analysis, pointwise products, longitude synthesis,
  * lift), on the same grids and with the same tables, so the result equals the

@@ -38,6 +38,7 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "cgtp_direct.h"
 #include "cgtp_internal.h"
 #include "device_common.h"
 
@@ -515,13 +516,7 @@ int launch_variant(const Tables<T>& tb, const int32_t* list, int64_t nblocks, in
 }
 
 template <typename T>
-int launch_bwd(const Tables<T>& tb, const BwdLaunch& bl, const T* x1, const T* x2, const T* g, T* gx1, T* gx2,
-               T* ws, int64_t N, int L, void* stream) {
-    int err = launch_variant<T, true>(tb, bl.block_list, bl.nsmall, bl.lds_small, x1, x2, g, ws, N, L, stream);
-    if (err) return err;
-    err = launch_variant<T, false>(tb, bl.block_list + bl.nsmall, bl.nlarge, bl.lds_large, x1, x2, g, ws, N, L,
-                                   stream);
-    if (err) return err;
+int launch_sums(const T* ws, T* gx1, T* gx2, int64_t N, int L, void* stream) {
     const int64_t rgrid = (2 * N * (int64_t)(L + 1) * (L + 1) + 255) / 256;
     if (rgrid <= 0) return 0;
     if (rgrid > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
@@ -530,7 +525,22 @@ int launch_bwd(const Tables<T>& tb, const BwdLaunch& bl, const T* x1, const T* x
     return (int)hipGetLastError();
 }
 
+template <typename T>
+int launch_bwd(const Tables<T>& tb, const BwdLaunch& bl, const T* x1, const T* x2, const T* g, T* gx1, T* gx2,
+               T* ws, int64_t N, int L, void* stream) {
+    int err = launch_variant<T, true>(tb, bl.block_list, bl.nsmall, bl.lds_small, x1, x2, g, ws, N, L, stream);
+    if (err) return err;
+    err = launch_variant<T, false>(tb, bl.block_list + bl.nsmall, bl.nlarge, bl.lds_large, x1, x2, g, ws, N, L,
+                                   stream);
+    if (err) return err;
+    return launch_sums<T>(ws, gx1, gx2, N, L, stream);
+}
+
 }  // namespace
+
+int launch_backward_sums(const float* ws, float* gx1, float* gx2, int64_t N, int L, void* stream) {
+    return launch_sums<float>(ws, gx1, gx2, N, L, stream);
+}
 
 int launch_backward_f32(const Tables<float>& tb, const BwdLaunch& bl, const float* x1, const float* x2,
                         const float* g, float* gx1, float* gx2, float* ws, int64_t N, int L, void* stream) {

@@ -100,6 +100,75 @@ template <> __host__ __device__ inline int dir_coef_index<double>(int k, int ord
     return 16 * k + 4 * order + row;
 }
 
+// ---------------------------------------------------------------- gradients (fp32)
+//
+// T_M[k] = sum over l3 of A_M[l3][k] g[l3, M] (the same matrices transposed, the
+// rows now k, the k steps l3 = lt, lt-1, ...), then
+//   grad_a[ma] += T_M[k] x_b[M - ma],   grad_b[M - ma] += T_M[k] x_a[ma].
+// One work-group takes the whole gradient runs of one stage (consecutive
+// blocks) for a tile of 32 / G pairs into LDS; a task is up to kDgRows groups
+// of four rows k of one block, which one wave takes through all orders, so
+// grad_a stays in its registers and grad_b in an LDS array of its own: every
+// sum has a fixed order.  G = 2, 4 or 8 groups of four orders per wave, so
+// that a block's run of 16, 8 or 4 pairs leaves room for several work-groups
+// per CU.
+constexpr int kDgThreads = 256;
+constexpr int kDgWaves = kDgThreads / 64;
+constexpr int kDgRows = 3;         // row groups per task
+constexpr int kDgClasses = 3;      // G = 2, 4, 8
+__host__ __device__ constexpr int dg_groups(int cls) { return 2 << cls; }
+__host__ __device__ constexpr int dg_pairs(int G) { return 32 / G; }
+__host__ __device__ constexpr int dg_kc(int G) { return 16 / G; }
+__host__ __device__ constexpr int dg_orders(int G) { return 4 * G; }
+__host__ __device__ constexpr int dg_row(int G) { return 2 * dg_pairs(G) + 1; }
+// zero rows before each degree and after the last: a task's last row group
+// reads up to three rows before its degree, and one row after a degree stands
+// for all orders past it
+constexpr int kDgPad = 3;
+__host__ __device__ inline int dg_tile_row(int l, int l0) { return kDgPad + l * l - l0 * l0 + kDgPad * (l - l0); }
+__host__ __device__ constexpr int dg_coef_index(int G, int k, int order, int row) {
+    return (((order >> 2) * dg_kc(G) + k) * 4 + row) * 4 + (order & 3);
+}
+
+struct alignas(16) DgTask {
+    int32_t chunk0;    // coefficients: [order group][chunk of k steps][row group]
+    int32_t code;      // la | lb << 8 | first row k0 << 16 | row groups << 24 | (l1 > l2) << 28
+    int32_t xa;        // tile element of (la, ma = la - k0); row k0 + i is i rows further down
+    int32_t xb;        // tile element of (lb, mb = -lb)
+    int32_t goff;      // g[l3, M] sits at goff + l3^2 + l3 + M of the stage's run
+    int32_t acca;      // first element of the task's rows of grad_a, [k][column]
+    int32_t accb;      // the task's grad_b, [lb + mb][column], one spare row at the end
+    int32_t pad;
+};
+
+struct alignas(16) DgBlock {
+    int32_t l1, l2;
+    int32_t acca;      // first element of grad_a, [k][column]
+    int32_t accb;      // first task's grad_b
+    int32_t ntasks;
+    int32_t stride;    // elements between the tasks' grad_b
+    int32_t pad[2];
+};
+
+struct alignas(16) DgStage {
+    int32_t off, len;            // run of one pair's outputs
+    int32_t task0, ntasks;       // heaviest first
+    int32_t block0, nblocks;
+    int32_t l1a, l1b, l2a, l2b;
+    int32_t x2tile, tile_len;    // elements; the run follows, then the sums
+    int32_t acc0, acc_len;       // the sums' first element and length
+    int32_t pad[2];
+};
+
+struct DgTables {
+    const float* coef;
+    const DgTask* tasks;
+    const DgBlock* blocks;
+    const DgStage* stages;       // by class
+    int32_t nstages[kDgClasses];
+    int32_t lds_bytes;
+};
+
 template <typename T> struct ChanArgs;
 
 // Weak, so that the plan's host code also links without the device code (it
@@ -108,5 +177,10 @@ __attribute__((weak)) int launch_direct_f32(const DirTables<float>& tb, const fl
                       const ChanArgs<float>* ch, bool real_basis, void* stream);
 __attribute__((weak)) int launch_direct_f64(const DirTables<double>& tb, const double* x1, const double* x2, double* out, int64_t N, int L,
                       const ChanArgs<double>* ch, bool real_basis, void* stream);
+
+__attribute__((weak)) int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2, const float* g,
+                                                 float* gx1, float* gx2, float* ws, int64_t N, int L, void* stream);
+// The sums of the blocks' contributions (cgtp_backward.hip).
+int launch_backward_sums(const float* ws, float* gx1, float* gx2, int64_t N, int L, void* stream);
 
 }  // namespace cgtp

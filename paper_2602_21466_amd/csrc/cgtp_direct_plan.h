@@ -209,4 +209,152 @@ void dir_build(int L, DirHost<T>& h) {
     h.lds_bytes = (int)lds;
 }
 
+struct DgHost {
+    std::vector<float> coef;
+    std::vector<DgTask> tasks;
+    std::vector<DgBlock> blocks;
+    std::vector<DgStage> stages;
+    int nstages[kDgClasses] = {0, 0, 0};
+    int lds_bytes = 0;
+};
+
+// Class of a block: the fewest groups of orders (least work on orders a block
+// does not have) whose run of gradients stays near 32 KiB per work-group.
+inline int dg_class(int l1, int l2) {
+    const int sz = (2 * l1 + 1) * (2 * l2 + 1);
+    return sz <= 512 ? 0 : sz <= 1100 ? 1 : 2;
+}
+
+// The gradient kernel's table and work lists of degree L.
+inline void dg_build(int L, DgHost& h) {
+    const int max_lds = 52 * 1024;   // stages of several blocks: three work-groups per CU
+    std::vector<std::vector<double>> cg;
+    std::map<std::pair<int, int>, std::vector<int>> first;   // (la, lb) -> first chunk of each task
+    for (int la = 0; la <= L; ++la)
+        for (int lb = la; lb <= L; ++lb) {
+            dir_cg_block(la, lb, cg);
+            const int G = dg_groups(dg_class(la, lb)), HM = dg_orders(G), KC = dg_kc(G);
+            const int nrg = (2 * la + 1 + 3) / 4;
+            for (int rg0 = 0; rg0 < nrg; rg0 += kDgRows) {
+                const int rgs = std::min(kDgRows, nrg - rg0);
+                first[{la, lb}].push_back((int)(h.coef.size() / kDirChunk));
+                for (int m0 = 0; m0 <= la + lb; m0 += HM) {
+                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
+                    if (nk <= 4 * rg0) break;
+                    const int nch = (nk + KC - 1) / KC;
+                    const size_t at = h.coef.size();
+                    h.coef.resize(at + (size_t)nch * rgs * kDirChunk, 0.0f);
+                    for (int o = 0; o < HM && m0 + o <= la + lb; ++o) {
+                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
+                        const auto& a = cg[(size_t)(m0 + o)];
+                        for (int s = 0; s < n; ++s)
+                            for (int r = 0; r < 4 * rgs && 4 * rg0 + r < n; ++r)
+                                h.coef[at + ((size_t)(s / KC) * rgs + r / 4) * kDirChunk +
+                                       dg_coef_index(G, s % KC, o, r % 4)] = (float)a[(size_t)s * n + 4 * rg0 + r];
+                    }
+                }
+            }
+        }
+    h.coef.resize(h.coef.size() + (size_t)kDgRows * kDirChunk, 0.0f);   // read ahead of the last chunk
+    const int nblk = (L + 1) * (L + 1);
+    std::vector<int> boff(nblk);
+    for (int b = 0, off = 0; b < nblk; ++b) {
+        boff[b] = off;
+        off += (2 * (b / (L + 1)) + 1) * (2 * (b % (L + 1)) + 1);
+    }
+    // stages: consecutive blocks of one class while their LDS fits
+    struct Cost {
+        DgStage s;
+        int64_t cost;
+    };
+    std::vector<Cost> by_class[kDgClasses];
+    for (int b0 = 0; b0 < nblk;) {
+        const int cls = dg_class(b0 / (L + 1), b0 % (L + 1)), G = dg_groups(cls), P = dg_pairs(G), RS = dg_row(G);
+        DgStage st{};
+        st.off = boff[b0];
+        st.l1a = st.l1b = b0 / (L + 1);
+        st.l2a = st.l2b = b0 % (L + 1);
+        int b1 = b0, acc_rows = 0;
+        auto tile = [&](int l1b, int l2a, int l2b) {
+            return (dg_tile_row(l1b + 1, st.l1a) + dg_tile_row(l2b + 1, l2a)) * RS;
+        };
+        auto lds = [&](int tile_len, int len, int rows) {
+            return 4 * (((tile_len + P * (len | 1) + 7) & ~3) + rows * 2 * P);
+        };
+        while (b1 < nblk) {
+            const int l1 = b1 / (L + 1), l2 = b1 % (L + 1), la = std::min(l1, l2), lb = std::max(l1, l2);
+            if (dg_class(l1, l2) != cls) break;
+            const int nrg = (2 * la + 4) / 4, nt = (nrg + kDgRows - 1) / kDgRows;
+            const int rows = 4 * nrg + nt * (2 * lb + 2);
+            const int len = st.len + (2 * l1 + 1) * (2 * l2 + 1);
+            const int l1b = std::max(st.l1b, l1), l2a = std::min(st.l2a, l2), l2b = std::max(st.l2b, l2);
+            if (b1 > b0 && lds(tile(l1b, l2a, l2b), len, acc_rows + rows) > max_lds) break;
+            st.len = len;
+            st.l1b = l1b;
+            st.l2a = l2a;
+            st.l2b = l2b;
+            acc_rows += rows;
+            ++b1;
+        }
+        st.x2tile = dg_tile_row(st.l1b + 1, st.l1a) * RS;
+        st.tile_len = (tile(st.l1b, st.l2a, st.l2b) + 3) & ~3;
+        st.acc0 = (st.tile_len + P * (st.len | 1) + 3) & ~3;
+        st.acc_len = acc_rows * 2 * P;
+        h.lds_bytes = std::max(h.lds_bytes, 4 * (st.acc0 + st.acc_len));
+        st.task0 = (int)h.tasks.size();
+        st.block0 = (int)h.blocks.size();
+        int64_t cost = 0;
+        int acc = st.acc0;
+        for (int b = b0; b < b1; ++b) {
+            const int l1 = b / (L + 1), l2 = b % (L + 1), la = std::min(l1, l2), lb = std::max(l1, l2);
+            const bool swap = l1 > l2;
+            const int t1 = dg_tile_row(l1, st.l1a) * RS, t2 = st.x2tile + dg_tile_row(l2, st.l2a) * RS;
+            const int nrg = (2 * la + 4) / 4, nt = (nrg + kDgRows - 1) / kDgRows;
+            const int stride = (2 * lb + 2) * 2 * P;
+            DgBlock bl{};
+            bl.l1 = l1;
+            bl.l2 = l2;
+            bl.acca = acc;
+            bl.accb = acc + 4 * nrg * 2 * P;
+            bl.ntasks = nt;
+            bl.stride = stride;
+            h.blocks.push_back(bl);
+            for (int t = 0; t < nt; ++t) {
+                DgTask k{};
+                const int k0 = 4 * kDgRows * t, rgs = std::min(kDgRows, nrg - kDgRows * t);
+                k.chunk0 = first[{la, lb}][(size_t)t];
+                k.code = la | lb << 8 | k0 << 16 | rgs << 24 | (swap ? 1 << 28 : 0);
+                k.xa = (swap ? t2 : t1) + (2 * la - k0) * RS;
+                k.xb = swap ? t1 : t2;
+                const int d = lb - la;
+                k.goff = boff[b] - st.off - d * d;
+                k.acca = bl.acca + k0 * 2 * P;
+                k.accb = bl.accb + t * stride;
+                h.tasks.push_back(k);
+                for (int m0 = 0; m0 <= la + lb; m0 += dg_orders(G)) {
+                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
+                    if (nk > k0) cost += (int64_t)rgs * nk + 8;
+                }
+            }
+            acc = bl.accb + nt * stride;
+        }
+        st.ntasks = (int)h.tasks.size() - st.task0;
+        st.nblocks = b1 - b0;
+        std::stable_sort(h.tasks.begin() + st.task0, h.tasks.end(), [](const DgTask& x, const DgTask& y) {
+            auto w = [](const DgTask& t) {   // rows x steps of the first orders, as a measure
+                const int la = t.code & 255, lb = t.code >> 8 & 255;
+                return ((t.code >> 24) & 15) * (2 * la + 1) * (la + lb + 1 - (t.code >> 16 & 255));
+            };
+            return w(x) > w(y);
+        });
+        by_class[cls].push_back({st, cost});
+        b0 = b1;
+    }
+    for (int c = 0; c < kDgClasses; ++c) {
+        std::stable_sort(by_class[c].begin(), by_class[c].end(), [](const Cost& x, const Cost& y) { return x.cost > y.cost; });
+        for (const auto& s : by_class[c]) h.stages.push_back(s.s);
+        h.nstages[c] = (int)by_class[c].size();
+    }
+}
+
 }  // namespace cgtp

@@ -368,6 +368,7 @@ struct cgtp_plan_s {
     void* dmem_dir = nullptr;
     cgtp::DirTables<float> df{};
     cgtp::DirTables<double> dd{};
+    cgtp::DgTables dg{};       // its gradients (fp32)
 };
 
 namespace {
@@ -418,6 +419,9 @@ template <typename T>
 int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std::vector<int32_t>& list) {
     const int L = p->L;
     const cgtp_grid& g = p->grid;
+    // fp32 plans of the direct contraction take only the facts about the method
+    // (grids, K, flops, which gradients exist) from here, not its tables
+    const bool tables = !p->direct || sizeof(T) == 8;
     // ---- grids: one Legendre table per distinct node count
     std::map<int, int> grid_lmax;          // n_theta -> largest degree needed
     std::map<int, int> grid_lmax_out;
@@ -433,6 +437,8 @@ int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std:
     std::map<int, std::array<int, 2>> grid_wtab_par;
     for (auto& kv : grid_lmax) {
         const int nt = kv.first, lmax = kv.second, R = nt / 2;
+        p->max_theta = std::max(p->max_theta, nt);
+        if (!tables) continue;
         std::vector<long double> x, w;
         gauss_legendre(nt, x, w);
         const int stride = (lmax + 1) * (lmax + 2) / 2;
@@ -462,7 +468,6 @@ int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std:
                     }
             h.wtab.insert(h.wtab.end(), (size_t)16, (T)0);
         }
-        p->max_theta = std::max(p->max_theta, nt);
     }
     for (auto& kv : phi_set) {
         const int n = kv.first;
@@ -591,6 +596,7 @@ int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std:
                 }
             }
             if (b.bwd_rings == 0) p->bwd_ok = false;
+            if (!tables) continue;
             // MFMA tiles in the order the waves take them: by |m|, row tile, column tile
             b.tdesc_off = (int)h.tdesc.size();
             {
@@ -887,13 +893,19 @@ template <typename T>
 int upload_direct(cgtp_plan_s* p, cgtp::DirTables<T>* tb) {
     cgtp::DirHost<T> h;
     cgtp::dir_build<T>(p->L, h);
-    const size_t n[4] = {h.coef.size() * sizeof(T), h.items.size() * sizeof(cgtp::DirItem),
-                         h.stages.size() * sizeof(cgtp::DirStage), h.groups.size() * sizeof(cgtp::DirGroup)};
-    const void* src[4] = {h.coef.data(), h.items.data(), h.stages.data(), h.groups.data()};
-    size_t offs[4], total = 0;
-    for (int i = 0; i < 4; ++i) {
-        offs[i] = total;
-        total = align_up(total + n[i], 256);
+    cgtp::DgHost d;   // gradients: fp32 (fp64 plans keep the sphere-grid kernel's)
+    if (sizeof(T) == 4) cgtp::dg_build(p->L, d);
+    struct Part {
+        const void* src;
+        size_t bytes, off;
+    };
+    auto part = [](const auto& v) { return Part{v.data(), v.size() * sizeof(v[0]), 0}; };
+    Part parts[8] = {part(h.coef), part(h.items), part(h.stages), part(h.groups),
+                     part(d.coef), part(d.tasks), part(d.blocks), part(d.stages)};
+    size_t total = 0;
+    for (auto& q : parts) {
+        q.off = total;
+        total = align_up(total + q.bytes, 256);
     }
     hipError_t e = hipMalloc(&p->dmem_dir, total);
     if (e != hipSuccess) {
@@ -902,19 +914,33 @@ int upload_direct(cgtp_plan_s* p, cgtp::DirTables<T>* tb) {
         return e == hipErrorOutOfMemory ? CGTP_ENOMEM : CGTP_EHIP;
     }
     char* base = (char*)p->dmem_dir;
-    for (int i = 0; i < 4; ++i) {
-        e = hipMemcpy(base + offs[i], src[i], n[i], hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            g_last_hip_error = (int)e;
-            return CGTP_EHIP;
-        }
+    auto copy = [&](size_t off, const void* src, size_t n) {
+        if (e == hipSuccess && n) e = hipMemcpy(base + off, src, n, hipMemcpyHostToDevice);
+    };
+    if (total <= ((size_t)1 << 20)) {   // small plans: one copy
+        std::vector<char> host(total, 0);
+        for (const auto& q : parts)
+            if (q.bytes) std::memcpy(host.data() + q.off, q.src, q.bytes);
+        copy(0, host.data(), total);
+    } else {
+        for (const auto& q : parts) copy(q.off, q.src, q.bytes);
     }
-    tb->coef = (const T*)(base + offs[0]);
-    tb->items = (const cgtp::DirItem*)(base + offs[1]);
-    tb->stages = (const cgtp::DirStage*)(base + offs[2]);
-    tb->groups = (const cgtp::DirGroup*)(base + offs[3]);
+    if (e != hipSuccess) {
+        g_last_hip_error = (int)e;
+        return CGTP_EHIP;
+    }
+    tb->coef = (const T*)(base + parts[0].off);
+    tb->items = (const cgtp::DirItem*)(base + parts[1].off);
+    tb->stages = (const cgtp::DirStage*)(base + parts[2].off);
+    tb->groups = (const cgtp::DirGroup*)(base + parts[3].off);
     tb->ngroups = (int32_t)h.groups.size();
     tb->lds_bytes = h.lds_bytes;
+    p->dg.coef = (const float*)(base + parts[4].off);
+    p->dg.tasks = (const cgtp::DgTask*)(base + parts[5].off);
+    p->dg.blocks = (const cgtp::DgBlock*)(base + parts[6].off);
+    p->dg.stages = (const cgtp::DgStage*)(base + parts[7].off);
+    for (int c = 0; c < cgtp::kDgClasses; ++c) p->dg.nstages[c] = d.nstages[c];
+    p->dg.lds_bytes = d.lds_bytes;
     return CGTP_OK;
 }
 
@@ -1023,6 +1049,7 @@ int cgtp_plan(int32_t L, const cgtp_grid* grid, cgtp_plan_t* plan_out) {
     if (!p) return CGTP_ENOMEM;
     p->L = L;
     p->grid = g;
+    p->direct = g.n_theta == 0 && g.n_phi == 0 && g.cover == CGTP_COVER_DEFAULT;
     hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -1034,15 +1061,13 @@ int cgtp_plan(int32_t L, const cgtp_grid* grid, cgtp_plan_t* plan_out) {
     if (g.dtype == CGTP_FP32) {
         HostTables<float> h;
         rc = build<float>(p, blocks, h, list);
-        if (rc == CGTP_OK) rc = upload<float>(p, blocks, h, list, &p->tf);
+        if (rc == CGTP_OK) rc = p->direct ? upload_direct<float>(p, &p->df) : upload<float>(p, blocks, h, list, &p->tf);
     } else {
         HostTables<double> h;
         rc = build<double>(p, blocks, h, list);
-        if (rc == CGTP_OK) rc = upload<double>(p, blocks, h, list, &p->td);
+        if (rc == CGTP_OK) rc = upload<double>(p, blocks, h, list, &p->td);   // direct plans: for the gradients
+        if (rc == CGTP_OK && p->direct) rc = upload_direct<double>(p, &p->dd);
     }
-    p->direct = g.n_theta == 0 && g.n_phi == 0 && g.cover == CGTP_COVER_DEFAULT;
-    if (rc == CGTP_OK && p->direct)
-        rc = g.dtype == CGTP_FP32 ? upload_direct<float>(p, &p->df) : upload_direct<double>(p, &p->dd);
     if (rc != CGTP_OK) {
         (void)cgtp_destroy(p);
         return rc;
@@ -1278,7 +1303,10 @@ int cgtp_backward(cgtp_plan_t plan, const void* x1, const void* x2, const void* 
     const cgtp::BwdLaunch bl{plan->d_bwd_list, plan->bwd_nsmall, nblocks - plan->bwd_nsmall, plan->bwd_lds_small,
                              plan->bwd_lds_large};
     int err;
-    if (plan->grid.dtype == CGTP_FP32)
+    if (plan->direct && plan->grid.dtype == CGTP_FP32)
+        err = cgtp::launch_direct_backward(plan->dg, (const float*)x1, (const float*)x2, (const float*)grad_out,
+                                           (float*)grad_x1, (float*)grad_x2, (float*)workspace, N, L, hip_stream);
+    else if (plan->grid.dtype == CGTP_FP32)
         err = cgtp::launch_backward_f32(plan->tf, bl, (const float*)x1, (const float*)x2, (const float*)grad_out,
                                         (float*)grad_x1, (float*)grad_x2, (float*)workspace, N, L, hip_stream);
     else

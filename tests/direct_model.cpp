@@ -2,7 +2,7 @@
 // every item of every group as the kernel does, with every index checked
 // against its buffer, and compares the outputs with the plain double sum over
 // the oracle's Racah-formula coefficients.
-//   usage: direct_model fp32|fp64 L
+//   usage: direct_model fp32|fp64|backward|cg L
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -99,6 +99,117 @@ static double run(int L) {
     return std::sqrt(num / den);
 }
 
+// The gradient kernel's lists (fp32), run task by task in the same way.
+static double backward(int L) {
+    DgHost h;
+    dg_build(L, h);
+    const int nin = (L + 1) * (L + 1), nout = nin * nin;
+    std::vector<double> x[2], grad[2], ref[2], g(nout);
+    for (int i = 0; i < 2; ++i) {
+        x[i].resize(nin);
+        grad[i].assign(nin, 0.0);
+        ref[i].assign(nin, 0.0);
+        for (auto& v : x[i]) v = drand48() - 0.5;
+    }
+    for (auto& v : g) v = drand48() - 0.5;
+    int si = 0, covered = 0;
+    for (int cls = 0; cls < kDgClasses; ++cls)
+        for (int i = 0; i < h.nstages[cls]; ++i, ++si) {
+            const DgStage& st = h.stages[(size_t)si];
+            const int G = dg_groups(cls), P = dg_pairs(G), RS = dg_row(G), HM = dg_orders(G), KC = dg_kc(G);
+            need(4 * (st.acc0 + st.acc_len) <= h.lds_bytes, "stage larger than the LDS of the launch");
+            need(st.tile_len + P * (st.len | 1) <= st.acc0, "run overlaps the sums");
+            covered += st.len;
+            std::vector<double> tile[2];
+            for (int s = 0; s < 2; ++s) {
+                tile[s].assign((size_t)st.tile_len, 0.0);
+                for (int in = 0; in < 2; ++in)
+                    for (int l = in ? st.l2a : st.l1a; l <= (in ? st.l2b : st.l1b); ++l)
+                        for (int m = -l; m <= l; ++m) {
+                            const int e = (in ? st.x2tile : 0) + (dg_tile_row(l, in ? st.l2a : st.l1a) + l + m) * RS;
+                            need(e >= 0 && e + RS - 1 <= (in ? st.tile_len : st.x2tile), "tile row outside its tile");
+                            tile[s][(size_t)e] = x[in][(size_t)(l * l + l + (s ? -m : m))];
+                        }
+            }
+            std::vector<double> sums[2];   // by sign of the order; element / (2 P) is the row
+            for (auto& v : sums) v.assign((size_t)st.acc_len, 0.0);
+            auto at = [&](int s, int e) -> double& {
+                need(e >= st.acc0 && e + 2 * P <= st.acc0 + st.acc_len, "sum outside the sums");
+                return sums[s][(size_t)(e - st.acc0)];
+            };
+            for (int ti = st.task0; ti < st.task0 + st.ntasks; ++ti) {
+                const DgTask& t = h.tasks[(size_t)ti];
+                const int la = t.code & 255, lb = t.code >> 8 & 255, k0 = t.code >> 16 & 255, rgs = t.code >> 24 & 15;
+                const int swap = t.code >> 28 & 1, lt = la + lb;
+                size_t ck = (size_t)t.chunk0;
+                for (int m0 = 0; m0 <= lt; m0 += HM) {
+                    const int nk = std::min(2 * la + 1, lt - m0 + 1);
+                    if (nk <= k0) break;
+                    for (int s = 0; s < 2; ++s)
+                        for (int o = 0; o < HM; ++o)
+                            for (int r = 0; r < 4 * rgs; ++r) {
+                                double T = 0;
+                                for (int k = 0; k < nk; ++k) {
+                                    const size_t ci = (ck + (size_t)(k / KC) * rgs + r / 4) * kDirChunk +
+                                                      (size_t)dg_coef_index(G, k % KC, o, r % 4);
+                                    need(ci < h.coef.size(), "read past the coefficients");
+                                    const int l3 = lt - k, M = m0 + o;
+                                    if (M > l3 || (s && !M)) continue;
+                                    const int q = t.goff + l3 * (l3 + 1) + (s ? -M : M);
+                                    need(q >= 0 && q < st.len, "gradient read outside the run");
+                                    T += ((k & 1) && s != swap ? -1.0 : 1.0) * (double)h.coef[ci] * g[(size_t)(st.off + q)];
+                                }
+                                const int d = std::min(lb - la + k0 + m0 + o + r, 2 * lb + 1);
+                                const int ea = t.xa - r * RS, eb = t.xb + d * RS;
+                                need(ea >= 0 && ea + 2 * P <= st.tile_len && eb >= 0 && eb + 2 * P <= st.tile_len,
+                                     "read past the tiles");
+                                if (m0 + o > lt) need(T == 0, "order past the block");
+                                at(s, t.acca + r * 2 * P) += T * tile[s][(size_t)eb];
+                                at(s, t.accb + d * 2 * P) += T * tile[s][(size_t)ea];
+                            }
+                    ck += (size_t)((nk + KC - 1) / KC * rgs);
+                }
+                need((ck + (size_t)rgs) * kDirChunk <= h.coef.size(), "read ahead past the coefficients");
+            }
+            for (int b = st.block0; b < st.block0 + st.nblocks; ++b) {
+                const DgBlock& bl = h.blocks[(size_t)b];
+                const bool swap = bl.l1 > bl.l2;
+                for (int in = 0; in < 2; ++in) {
+                    const int l = in ? bl.l2 : bl.l1;
+                    for (int m = -l; m <= l; ++m) {
+                        double v = 0;
+                        if ((in == 0) != swap)
+                            v = at(0, bl.acca + (l - m) * 2 * P) + at(1, bl.acca + (l + m) * 2 * P);
+                        else
+                            for (int t = 0; t < bl.ntasks; ++t)
+                                v += at(0, bl.accb + t * bl.stride + (l + m) * 2 * P) +
+                                     at(1, bl.accb + t * bl.stride + (l - m) * 2 * P);
+                        grad[in][(size_t)(l * l + l + m)] += v;
+                    }
+                }
+            }
+        }
+    need(covered == nout, "stages do not cover the outputs");
+    int off = 0;
+    for (int l1 = 0; l1 <= L; ++l1)
+        for (int l2 = 0; l2 <= L; ++l2)
+            for (int l3 = std::abs(l1 - l2); l3 <= l1 + l2; ++l3)
+                for (int m3 = -l3; m3 <= l3; ++m3, ++off)
+                    for (int m1 = std::max(-l1, m3 - l2); m1 <= std::min(l1, m3 + l2); ++m1) {
+                        const double c = oracle_cg(l1, m1, l2, m3 - m1, l3, m3) * g[(size_t)off];
+                        const size_t i1 = (size_t)(l1 * l1 + l1 + m1), i2 = (size_t)(l2 * l2 + l2 + m3 - m1);
+                        ref[0][i1] += c * x[1][i2];
+                        ref[1][i2] += c * x[0][i1];
+                    }
+    double num = 0, den = 0;
+    for (int in = 0; in < 2; ++in)
+        for (int i = 0; i < nin; ++i) {
+            num += (grad[in][(size_t)i] - ref[in][(size_t)i]) * (grad[in][(size_t)i] - ref[in][(size_t)i]);
+            den += ref[in][(size_t)i] * ref[in][(size_t)i];
+        }
+    return std::sqrt(num / den);
+}
+
 // Largest error of the plan's coefficients against the oracle's.
 static double coefficients(int L) {
     double worst = 0;
@@ -118,9 +229,10 @@ static double coefficients(int L) {
 }
 
 int main(int argc, char** argv) {
-    need(argc == 3, "usage: direct_model fp32|fp64|cg L");
+    need(argc == 3, "usage: direct_model fp32|fp64|backward|cg L");
     const int L = std::atoi(argv[2]);
-    const double e = !std::strcmp(argv[1], "cg") ? coefficients(L) : !std::strcmp(argv[1], "fp64") ? run<double>(L) : run<float>(L);
+    const bool fp64 = !std::strcmp(argv[1], "fp64"), bwd = !std::strcmp(argv[1], "backward");
+    const double e = !std::strcmp(argv[1], "cg") ? coefficients(L) : bwd ? backward(L) : fp64 ? run<double>(L) : run<float>(L);
     std::printf("%.17g\n", e);
     return 0;
 }

@@ -41,9 +41,10 @@ def test_coefficients_match_the_racah_formula(model):
 
 
 @pytest.mark.parametrize("dtype,L", [("fp32", 0), ("fp32", 1), ("fp32", 2), ("fp32", 4), ("fp32", 7), ("fp32", 11),
-                                     ("fp32", 16), ("fp64", 0), ("fp64", 3), ("fp64", 8)])
+                                     ("fp32", 16), ("fp64", 0), ("fp64", 3), ("fp64", 8),
+                                     ("backward", 0), ("backward", 3), ("backward", 8), ("backward", 17)])
 def test_work_lists_cover_every_output_once(model, dtype, L):
-    assert model(dtype, L) < TOL[dtype]
+    assert model(dtype, L) < TOL.get(dtype, 1e-6)
 
 
 def _rel(a, b):
@@ -73,6 +74,26 @@ def test_forward_and_real_match_oracle(L, N, dtype):
     r = plan.forward_real(x1.cuda(), x2.cuda()).double().cpu().numpy()
     assert _rel(z, oracle.cgtp(L, a, b)) < TOL[dtype]
     assert _rel(r, oracle.cgtp_real(L, a, b)) < TOL[dtype]
+    plan.close()
+
+
+# ragged tiles of 16, 8 and 4 pairs (the three classes of blocks: largest degrees up to 11, 16 and above)
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,N", [(0, 1), (1, 17), (3, 15), (6, 33), (11, 16), (13, 9), (16, 8), (18, 5)])
+def test_gradients_match_oracle(L, N):
+    import torch
+    import oracle
+    import paper_2602_21466_amd as lib
+    print("case L=%d N=%d" % (L, N), flush=True)
+    x1, x2 = _rows(torch, N, (L + 1) ** 2, "fp32", L), _rows(torch, N, (L + 1) ** 2, "fp32", 100 + L)
+    g = _rows(torch, N, (L + 1) ** 4, "fp32", 200 + L)
+    plan = lib.Plan(L)
+    a = plan.backward(x1.cuda(), x2.cuda(), g.cuda())
+    b = plan.backward(x1.cuda(), x2.cuda(), g.cuda())
+    ref = oracle.cgtp_backward(L, x1.double().numpy(), x2.double().numpy(), g.double().numpy())
+    for u, v, r in zip(a, b, ref):
+        assert torch.equal(u, v)   # every sum has a fixed order
+        assert _rel(u.double().cpu().numpy(), r) < TOL["fp32"]
     plan.close()
 
 
