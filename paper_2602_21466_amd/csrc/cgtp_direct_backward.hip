@@ -127,23 +127,32 @@ __device__ __forceinline__ void dg_task(const DgTask& t, const float* __restrict
         // ---- T[k0 + i][m0 + gm + mi] = acc[i / 4][mi][i % 4]: both gradients
         const float* xb = smem + t.xb + col;
         const int d0 = lb - la + k0 + m0 + gm;   // row lb + mb of i = mi = 0
+        // grad_b is added to four rows at a time: within four, the groups of orders
+        // add to different rows (except past the degree, in the spare one), and a
+        // wave's LDS accesses are in order.  (Plain reads and writes: an LDS float
+        // atomic takes about as long as ten of them.)
 #pragma unroll
-        for (int i = 0; i < NR + 3; ++i) {
-            const int d = min(d0 + i, 2 * lb + 1);   // (past the degree: the zero and spare row)
-            const float xbv = xb[d * RS];
-            float v = 0.0f;
+        for (int i0 = 0; i0 < NR + 3; i0 += 4) {
+            float v[4], *dst[4];
 #pragma unroll
-            for (int mi = 0; mi < 4; ++mi) {
-                const int k = i - mi;
-                if (k < 0 || k >= NR) continue;
-                const float tv = acc[k >> 2][mi][k & 3];
-                ga[k] = fmaf(tv, xbv, ga[k]);
-                v = fmaf(tv, xa[-k * RS], v);
+            for (int u = 0; u < 4 && i0 + u < NR + 3; ++u) {
+                const int i = i0 + u;
+                const int d = min(d0 + i, 2 * lb + 1);   // (past the degree: the zero and spare row)
+                const float xbv = xb[d * RS];
+                dst[u] = accb + d * 2 * P;
+                v[u] = *dst[u];
+#pragma unroll
+                for (int mi = 0; mi < 4; ++mi) {
+                    const int k = i - mi;
+                    if (k < 0 || k >= NR) continue;
+                    const float tv = acc[k >> 2][mi][k & 3];
+                    ga[k] = fmaf(tv, xbv, ga[k]);
+                    v[u] = fmaf(tv, xa[-k * RS], v[u]);
+                }
             }
-            // within one instruction the groups of orders add to different rows
-            // (except in the spare one), and the wave's instructions are in order
-            float* dst = accb + d * 2 * P;
-            __hip_atomic_fetch_add(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+            for (int u = 0; u < 4 && i0 + u < NR + 3; ++u) *dst[u] = v[u];
+            asm volatile("" ::: "memory");   // the next four rows are read after these are written
         }
     }
     // grad_a: summed over the groups of orders
