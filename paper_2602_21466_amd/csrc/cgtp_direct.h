@@ -92,6 +92,14 @@ struct DirTables {
 
 // fp32 coefficients of a chunk: element (lane, mi) at 4 lane + mi with
 // lane = ((group of orders) kc + k) 4 + row; fp64: (k, mi, row) at 16 k + 4 mi + row.
+// Elements from one pair's run in LDS to the next: room for its offset from a
+// 16-byte boundary, and an odd number of 16-byte units, so that the pairs of a
+// wave start on different banks.
+template <typename T> __host__ __device__ inline int dir_run(int len) {
+    const int v = 16 / (int)sizeof(T);
+    return ((len + v - 1 + v - 1) / v | 1) * v;
+}
+
 template <typename T> __host__ __device__ inline int dir_coef_index(int k, int order, int row);
 template <> __host__ __device__ inline int dir_coef_index<float>(int k, int order, int row) {
     return (((order >> 2) * dir_kc<float>() + k) * 4 + row) * 4 + (order & 3);
@@ -105,22 +113,31 @@ template <> __host__ __device__ inline int dir_coef_index<double>(int k, int ord
 // T_M[k] = sum over l3 of A_M[l3][k] g[l3, M] (the same matrices transposed, the
 // rows now k, the k steps l3 = lt, lt-1, ...), then
 //   grad_a[ma] += T_M[k] x_b[M - ma],   grad_b[M - ma] += T_M[k] x_a[ma].
-// One work-group takes the whole gradient runs of one stage (consecutive
-// blocks) for a tile of 32 / G pairs into LDS; a task is up to kDgRows groups
-// of four rows k of one block, which one wave takes through all orders, so
-// grad_a stays in its registers and grad_b in an LDS array of its own: every
-// sum has a fixed order.  G = 2, 4 or 8 groups of four orders per wave, so
-// that a block's run of 16, 8 or 4 pairs leaves room for several work-groups
-// per CU.
+// One work-group takes the gradient runs of one stage (consecutive blocks, or
+// one large block in parts of some degrees l3 each) for a tile of 32 / G pairs
+// into LDS; a task is up to kDgRows groups of four rows k of one block, which
+// one wave takes through all orders, so grad_a stays in its registers and
+// grad_b in an LDS array of its own: every sum has a fixed order.  G = 2 or 4
+// groups of four orders per wave, so that the runs of 16 or 8 pairs leave room
+// for two or three work-groups per CU.  (Measured at L = 16, N = 8192: 200
+// outputs as the limit of G = 2 2420 us, 512 2692, 1100 4478; at L = 32,
+// N = 1024: large blocks with 52 KiB of LDS 7994 us, 79 KiB 5143.)
 constexpr int kDgThreads = 256;
 constexpr int kDgWaves = kDgThreads / 64;
 constexpr int kDgRows = 3;         // row groups per task
-constexpr int kDgClasses = 3;      // G = 2, 4, 8
-__host__ __device__ constexpr int dg_groups(int cls) { return 2 << cls; }
+// Classes of blocks: up to 200 outputs with G = 2, the others with G = 4; those
+// above 1100 outputs in parts, with two work-groups per CU (fewer parts: each
+// costs another round of the two gradients) and a launch of their own.
+constexpr int kDgClasses = 3;
+__host__ __device__ constexpr int dg_class(int l1, int l2) {
+    return (2 * l1 + 1) * (2 * l2 + 1) <= 200 ? 0 : (2 * l1 + 1) * (2 * l2 + 1) <= 1100 ? 1 : 2;
+}
+__host__ __device__ constexpr int dg_groups(int cls) { return cls == 0 ? 2 : 4; }
 __host__ __device__ constexpr int dg_pairs(int G) { return 32 / G; }
 __host__ __device__ constexpr int dg_kc(int G) { return 16 / G; }
 __host__ __device__ constexpr int dg_orders(int G) { return 4 * G; }
-__host__ __device__ constexpr int dg_row(int G) { return 2 * dg_pairs(G) + 1; }
+__host__ __device__ constexpr int dg_row(int G) { return 2 * dg_pairs(G) + 1; }   // row of the tiles and the sums
+constexpr int kDgMaxInputs = 192;  // inputs a stage may read per pair (both tiles)
 // zero rows before each degree and after the last: a task's last row group
 // reads up to three rows before its degree, and one row after a degree stands
 // for all orders past it
@@ -141,32 +158,39 @@ struct alignas(16) DgTask {
     int32_t pad;
 };
 
-struct alignas(16) DgBlock {
-    int32_t l1, l2;
-    int32_t acca;      // first element of grad_a, [k][column]
-    int32_t accb;      // first task's grad_b
-    int32_t ntasks;
-    int32_t stride;    // elements between the tasks' grad_b
-    int32_t pad[2];
+// One component of a block's two gradient rows: the sum over both order signs
+// (and, for grad_b, the tasks) of elements plus + t stride, minus + t stride.
+struct alignas(16) DgOut {
+    int32_t plus, minus;
+    int32_t code;      // tasks | stride << 4 | component << 20
+    int32_t ws;        // the block's offset per pair in the workspace | its components << 20
+};
+
+// Some degrees of a stage: steps s0 .. s1-1 of its tasks.
+struct alignas(16) DgPart {
+    int32_t off, len;            // run of one pair's outputs
+    int32_t s0, s1;
 };
 
 struct alignas(16) DgStage {
-    int32_t off, len;            // run of one pair's outputs
+    int32_t off;                 // of the tasks' goff
+    int32_t part0, nparts;
     int32_t task0, ntasks;       // heaviest first
-    int32_t block0, nblocks;
+    int32_t out0, nouts;
     int32_t l1a, l1b, l2a, l2b;
     int32_t x2tile, tile_len;    // elements; the run follows, then the sums
-    int32_t acc0, acc_len;       // the sums' first element and length
-    int32_t pad[2];
+    int32_t acc0, acc_len;       // the sums' first element and length (multiples of 4)
+    int32_t pad;
 };
 
 struct DgTables {
     const float* coef;
     const DgTask* tasks;
-    const DgBlock* blocks;
+    const DgOut* outs;
+    const DgPart* parts;
     const DgStage* stages;       // by class
     int32_t nstages[kDgClasses];
-    int32_t lds_bytes;
+    int32_t lds_bytes[kDgClasses];
 };
 
 template <typename T> struct ChanArgs;

@@ -9,6 +9,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "cgtp_direct.h"
@@ -23,23 +24,26 @@ using namespace ::cgtp::dev;
 struct DgArgs {
     const float* __restrict__ coef;
     const DgTask* __restrict__ tasks;
-    const DgBlock* __restrict__ blocks;
+    const DgOut* __restrict__ outs;
+    const DgPart* __restrict__ parts;
     const DgStage* __restrict__ stages;
     const float* __restrict__ x1;
     const float* __restrict__ x2;
     const float* __restrict__ g;
     float* __restrict__ ws;
     int64_t N;
-    int64_t nunits[kDgClasses];       // stages x tiles of pairs
-    int64_t wg0[kDgClasses + 1];      // first work-group of each class
-    int32_t stage0[kDgClasses];
-    int32_t chunk[kDgClasses];        // consecutive units given to one XCD
+    // the classes of one launch
+    int32_t ncls;
+    int32_t G[2], stage0[2];
+    int64_t nunits[2];       // stages x tiles of pairs
+    int64_t wg0[3];          // first work-group of each class
+    int32_t chunk[2];        // consecutive units given to one XCD
     int32_t L;
 };
 
 template <int G, int J> __device__ __forceinline__ f32x4 dg_mfma(float a, float b, f32x4 c) {
     // the coefficients of step J, four rows, broadcast to the columns of each group of orders
-    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, G == 2 ? 3 : G == 4 ? 2 : 1, J, 0);
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, G == 2 ? 3 : 2, J, 0);
 }
 
 // Steps J .. of one chunk.  MASK: some orders may exceed the degree, or the
@@ -70,11 +74,11 @@ __device__ __forceinline__ void dg_steps(const f32x4 (&a)[RG], const float* cons
 }
 
 template <int G, int RG>
-__device__ __forceinline__ void dg_task(const DgTask& t, const float* __restrict__ coef, float* smem, const float* run,
-                                        int ps, int lane) {
+__device__ __forceinline__ void dg_task(const DgTask& t, const DgPart& part, const float* __restrict__ coef, float* smem,
+                                        const float* run, int lane) {
     constexpr int P = dg_pairs(G), KC = dg_kc(G), RS = dg_row(G), HM = dg_orders(G), NR = 4 * RG;
     static_assert(KC % 2 == 0, "a chunk starts at an even step");
-    const int col = lane & (2 * P - 1), gm = 4 * (lane / (2 * P)), pr = col & (P - 1);
+    const int col = lane & (2 * P - 1), gm = 4 * (lane / (2 * P));
     const bool neg = col >= P;
     const int la = t.code & 255, lb = (t.code >> 8) & 255, k0 = (t.code >> 16) & 255;
     const bool swap = (t.code >> 28) & 1;
@@ -84,11 +88,14 @@ __device__ __forceinline__ void dg_task(const DgTask& t, const float* __restrict
 #pragma unroll
     for (int i = 0; i < NR; ++i) ga[i] = 0.0f;
     const float* xa = smem + t.xa + col;   // row i at -i RS
-    const float* cf = coef + (size_t)t.chunk0 * kDirChunk + 4 * lane;
+    const float* cf0 = coef + (size_t)t.chunk0 * kDirChunk + 4 * lane;
     float* accb = smem + t.accb + col;
     for (int m0 = 0; m0 <= lt; m0 += HM) {
         const int nk = min(2 * la + 1, lt - m0 + 1);
-        if (nk <= k0) break;
+        if (nk <= k0 || nk <= part.s0) break;   // (nk falls with m0)
+        const int s1 = min(nk, part.s1);        // the part's steps
+        const float* cf = cf0 + (size_t)(part.s0 / KC) * RG * kDirChunk;
+        cf0 += (size_t)((nk + KC - 1) / KC) * RG * kDirChunk;
         f32x4 acc[RG][4];
 #pragma unroll
         for (int r = 0; r < RG; ++r)
@@ -96,14 +103,14 @@ __device__ __forceinline__ void dg_task(const DgTask& t, const float* __restrict
             for (int mi = 0; mi < 4; ++mi) acc[r][mi] = f32x4(0);
         const float* gp[4];
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) gp[mi] = run + pr * ps + t.goff + sg * (m0 + gm + mi);
+        for (int mi = 0; mi < 4; ++mi) gp[mi] = run + t.goff + sg * (m0 + gm + mi);
         // chunks in which every order of the item has its degrees, then the others; the
         // next chunk's coefficients are loaded a chunk ahead (the table ends in spare ones)
-        const int nfull = max(min(nk, lt - (m0 + HM - 1) + 1), 0) / KC * KC;
+        const int nfull = part.s0 + max(min(s1, lt - (m0 + HM - 1) + 1) - part.s0, 0) / KC * KC;
         f32x4 a[RG], an[RG];
 #pragma unroll
         for (int r = 0; r < RG; ++r) a[r] = *reinterpret_cast<const f32x4*>(cf + r * kDirChunk);
-        int s = 0;
+        int s = part.s0;
         for (; s < nfull; s += KC) {
             cf += RG * kDirChunk;
 #pragma unroll
@@ -112,11 +119,11 @@ __device__ __forceinline__ void dg_task(const DgTask& t, const float* __restrict
 #pragma unroll
             for (int r = 0; r < RG; ++r) a[r] = an[r];
         }
-        for (; s < nk; s += KC) {
+        for (; s < s1; s += KC) {
             cf += RG * kDirChunk;
 #pragma unroll
             for (int r = 0; r < RG; ++r) an[r] = *reinterpret_cast<const f32x4*>(cf + r * kDirChunk);
-            dg_steps<G, RG, 0, true>(a, gp, lt - s, nk - s, m0 + gm, f_odd, acc);
+            dg_steps<G, RG, 0, true>(a, gp, lt - s, s1 - s, m0 + gm, f_odd, acc);
 #pragma unroll
             for (int r = 0; r < RG; ++r) a[r] = an[r];
         }
@@ -139,7 +146,7 @@ __device__ __forceinline__ void dg_task(const DgTask& t, const float* __restrict
                 const int i = i0 + u;
                 const int d = min(d0 + i, 2 * lb + 1);   // (past the degree: the zero and spare row)
                 const float xbv = xb[d * RS];
-                dst[u] = accb + d * 2 * P;
+                dst[u] = accb + d * RS;
                 v[u] = *dst[u];
 #pragma unroll
                 for (int mi = 0; mi < 4; ++mi) {
@@ -155,12 +162,12 @@ __device__ __forceinline__ void dg_task(const DgTask& t, const float* __restrict
             asm volatile("" ::: "memory");   // the next four rows are read after these are written
         }
     }
-    // grad_a: summed over the groups of orders
+    // grad_a: summed over the groups of orders (and the parts)
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
 #pragma unroll
         for (int o = 2 * P; o < 64; o *= 2) ga[i] += __shfl_xor(ga[i], o);
-        if (gm == 0) smem[t.acca + i * 2 * P + col] = ga[i];
+        if (gm == 0) smem[t.acca + i * RS + col] += ga[i];
     }
 }
 
@@ -172,75 +179,98 @@ __device__ __forceinline__ void dg_stage(const DgArgs& ar, const DgStage& st, in
     const int np = (int)(ar.N - p0 < P ? ar.N - p0 : P);
     const int nin = (ar.L + 1) * (ar.L + 1);
     const int64_t nout = (int64_t)nin * nin;
-    const int ps = st.len | 1;
     float* run = smem + st.tile_len;
-    for (int e = tid * 4; e < st.tile_len; e += kDgThreads * 4) *reinterpret_cast<f32x4*>(smem + e) = f32x4(0);
-    for (int e = st.acc0 + tid * 4; e < st.acc0 + st.acc_len; e += kDgThreads * 4)
-        *reinterpret_cast<f32x4*>(smem + e) = f32x4(0);
-    lds_barrier();
-    for (int p = wave; p < np; p += kDgWaves) {
-        const float* src = ar.g + (p0 + p) * nout + st.off;
-        float* dst = run + p * ps;
-        for (int i0 = 0; i0 < st.len; i0 += 8 * 64) {   // eight loads in flight per lane
-            float v[8];
+    // the run of a part, 16 bytes at a time: it starts as far from a 16-byte boundary
+    // in LDS as in memory
+    auto load_run = [&](const DgPart& part, int ps) {
+        for (int p = wave; p < np; p += kDgWaves) {
+            const int64_t o = (p0 + p) * nout + part.off;
+            const int sh = (int)(o & 3), end = sh + part.len;
+            const float* src = ar.g + (o - sh);
+            float* dst = run + p * ps;
+            for (int i0 = 4 * lane; i0 < end; i0 += 4 * 256) {   // four loads in flight per lane
+                f32x4 v[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + 64 * u + lane;
-                v[u] = i < st.len ? __builtin_nontemporal_load(src + i) : 0.0f;
-            }
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + 256 * u;
+                    if (i + 4 <= end)
+                        v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + i));
+                    else {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + 64 * u + lane;
-                if (i < st.len) dst[i] = v[u];
-            }
-        }
+                        for (int q = 0; q < 4; ++q) v[u][q] = i + q < end ? src[i + q] : 0.0f;
+                    }
+                }
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int la = s ? st.l2a : st.l1a, lb = s ? st.l2b : st.l1b;
-            const float* xs = (s ? ar.x2 : ar.x1) + (p0 + p) * nin;
-            float* tile = smem + (s ? st.x2tile : 0);
-            for (int i = la * la + lane; i < (lb + 1) * (lb + 1); i += 64) {
-                const int l = (int)__builtin_sqrtf((float)i + 0.5f);   // exact for i < 2^20
-                const int m = i - l * l - l;
-                const float v = xs[i];
-                float* t0 = tile + (dg_tile_row(l, la) + l) * RS + p;   // order 0
-                t0[m * RS] = v;
-                t0[-m * RS + P] = v;   // the second set of columns: orders reversed
-            }
-        }
-    }
-    lds_barrier();
-    for (int ti = wave; ti < st.ntasks; ti += kDgWaves) {
-        const DgTask t = ar.tasks[st.task0 + ti];
-        switch ((t.code >> 24) & 15) {
-            case 1: dg_task<G, 1>(t, ar.coef, smem, run, ps, lane); break;
-            case 2: dg_task<G, 2>(t, ar.coef, smem, run, ps, lane); break;
-            default: dg_task<G, 3>(t, ar.coef, smem, run, ps, lane); break;
-        }
-    }
-    lds_barrier();
-    // ---- per block: both order signs, grad_b over the tasks in order
-    for (int b = st.block0; b < st.block0 + st.nblocks; ++b) {
-        const DgBlock bl = ar.blocks[b];
-        const int n1 = 2 * bl.l1 + 1, n2 = 2 * bl.l2 + 1, nrow = n1 + n2;
-        const bool swap = bl.l1 > bl.l2;
-        float* dst = ar.ws + bwd_block_off(ar.L, bl.l1, bl.l2) * ar.N + p0 * nrow;
-        for (int e = tid; e < np * nrow; e += kDgThreads) {
-            const int p = e / nrow, ee = e - p * nrow;
-            const bool first = ee < n1;
-            const int l = first ? bl.l1 : bl.l2, m = (first ? ee : ee - n1) - l;
-            float v;
-            if (first != swap) {   // the smaller degree's input (x1 if equal)
-                const float* a = smem + bl.acca + p;
-                v = a[(l - m) * 2 * P] + a[(l + m) * 2 * P + P];
-            } else {
-                v = 0.0f;
-                for (int t = 0; t < bl.ntasks; ++t) {
-                    const float* a = smem + bl.accb + t * bl.stride + p;
-                    v += a[(l + m) * 2 * P] + a[(l - m) * 2 * P + P];
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + 256 * u;
+                    if (i < end) *reinterpret_cast<f32x4*>(dst + i) = v[u];
                 }
             }
-            dst[e] = v;
+        }
+    };
+    // ---- input tiles (TP threads per pair, all of a thread's loads in flight), zero
+    // rows around the degrees, cleared sums
+    {
+        constexpr int TP = kDgThreads / P, kX = (kDgMaxInputs + TP - 1) / TP;
+        const int e1 = (st.l1b + 1) * (st.l1b + 1) - st.l1a * st.l1a, e2 = (st.l2b + 1) * (st.l2b + 1) - st.l2a * st.l2a;
+        const int xp = tid / TP, xi = tid & (TP - 1);
+        const int64_t row = p0 + xp < ar.N ? p0 + xp : ar.N - 1;   // (columns past N are not written out)
+        const float* r1 = ar.x1 + row * nin + st.l1a * st.l1a;
+        const float* r2 = ar.x2 + row * nin + st.l2a * st.l2a - e1;
+        float xv[kX];
+#pragma unroll
+        for (int u = 0; u < kX; ++u) {
+            const int i = xi + u * TP;
+            if (i < e1 + e2) xv[u] = (i < e1 ? r1 : r2)[i];
+        }
+        for (int e = st.acc0 + tid * 4; e < st.acc0 + st.acc_len; e += kDgThreads * 4)
+            *reinterpret_cast<f32x4*>(smem + e) = f32x4(0);
+        for (int s = 0; s < 2; ++s) {
+            const int la = s ? st.l2a : st.l1a, lb = s ? st.l2b : st.l1b;
+            float* t0 = smem + (s ? st.x2tile : 0);
+            for (int l = la; l <= lb + 1; ++l)   // the rows before degree l
+                for (int e = tid; e < kDgPad * RS; e += kDgThreads) t0[(dg_tile_row(l, la) - kDgPad) * RS + e] = 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kX; ++u) {
+            const int i = xi + u * TP;
+            if (i >= e1 + e2) break;
+            const int l0 = i < e1 ? st.l1a : st.l2a, ci = i < e1 ? i + l0 * l0 : i - e1 + l0 * l0;
+            const int l = (int)__builtin_sqrtf((float)ci + 0.5f);   // exact for ci < 2^20
+            const int m = ci - l * l - l;
+            float* t0 = smem + (i < e1 ? 0 : st.x2tile) + (dg_tile_row(l, l0) + l) * RS + xp;   // order 0
+            t0[m * RS] = xv[u];
+            t0[-m * RS + P] = xv[u];   // the second set of columns: orders reversed
+        }
+    }
+    const int pr = lane & (P - 1);
+    for (int pi = 0; pi < st.nparts; ++pi) {
+        const DgPart part = ar.parts[st.part0 + pi];
+        const int ps = dir_run<float>(part.len);
+        load_run(part, ps);
+        lds_barrier();
+        // the lane's pair's run, from the stage's first output
+        const float* lrun = run + pr * ps + (int)(((p0 + pr) * nout + part.off) & 3) - (part.off - st.off);
+        for (int ti = wave; ti < st.ntasks; ti += kDgWaves) {
+            const DgTask t = ar.tasks[st.task0 + ti];
+            switch ((t.code >> 24) & 15) {
+                case 1: dg_task<G, 1>(t, part, ar.coef, smem, lrun, lane); break;
+                case 2: dg_task<G, 2>(t, part, ar.coef, smem, lrun, lane); break;
+                default: dg_task<G, 3>(t, part, ar.coef, smem, lrun, lane); break;
+            }
+        }
+        lds_barrier();
+    }
+    // ---- the blocks' gradient rows: both order signs, grad_b over the tasks in order
+    for (int r = tid; r < st.nouts; r += kDgThreads) {
+        const DgOut o = ar.outs[st.out0 + r];
+        const int nt = o.code & 15, stride = (o.code >> 4) & 0xffff, e = (o.code >> 20) & 0xff;
+        const int nrow = o.ws >> 20;
+        float* dst = ar.ws + (int64_t)(o.ws & 0xfffff) * ar.N + p0 * nrow + e;
+        for (int p = 0; p < np; ++p) {
+            float v = 0.0f;
+            for (int t = 0; t < nt; ++t) v += smem[o.plus + t * stride + p] + smem[o.minus + t * stride + p];
+            dst[(int64_t)p * nrow] = v;
         }
     }
 }
@@ -248,22 +278,19 @@ __device__ __forceinline__ void dg_stage(const DgArgs& ar, const DgStage& st, in
 __global__ __launch_bounds__(kDgThreads, 3) void direct_backward_kernel(const DgArgs ar) {
     extern __shared__ __align__(16) unsigned char dg_smem[];
     float* smem = reinterpret_cast<float*>(dg_smem);
-    int c = 0;
-    while (c + 1 < kDgClasses && (int64_t)blockIdx.x >= ar.wg0[c + 1]) ++c;
+    const int c = ar.ncls > 1 && (int64_t)blockIdx.x >= ar.wg0[1] ? 1 : 0;
     // (work-groups of a class start at a multiple of 8: work-group i runs on XCD i mod 8)
     const int64_t i = blockIdx.x - ar.wg0[c], xcd = i & 7, j = i >> 3, ck = j / ar.chunk[c];
     const int64_t unit = (ck * 8 + xcd) * ar.chunk[c] + (j - ck * ar.chunk[c]);
     if (unit >= ar.nunits[c]) return;
-    const int P = dg_pairs(dg_groups(c));
+    const int P = dg_pairs(ar.G[c]);
     const int64_t ntiles = (ar.N + P - 1) / P, si = unit / ntiles;
     const DgStage st = ar.stages[ar.stage0[c] + si];
     const int64_t p0 = (unit - si * ntiles) * P;
-    if (c == 0)
+    if (ar.G[c] == 2)
         dg_stage<2>(ar, st, p0, smem);
-    else if (c == 1)
-        dg_stage<4>(ar, st, p0, smem);
     else
-        dg_stage<8>(ar, st, p0, smem);
+        dg_stage<4>(ar, st, p0, smem);
 }
 
 }  // namespace
@@ -273,7 +300,8 @@ int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2,
     DgArgs ar{};
     ar.coef = tb.coef;
     ar.tasks = tb.tasks;
-    ar.blocks = tb.blocks;
+    ar.outs = tb.outs;
+    ar.parts = tb.parts;
     ar.stages = tb.stages;
     ar.x1 = x1;
     ar.x2 = x2;
@@ -281,26 +309,35 @@ int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2,
     ar.ws = ws;
     ar.N = N;
     ar.L = L;
-    int s0 = 0;
-    for (int c = 0; c < kDgClasses; ++c) {
-        const int P = dg_pairs(dg_groups(c));
-        ar.stage0[c] = s0;
-        s0 += tb.nstages[c];
-        ar.nunits[c] = (N + P - 1) / P * tb.nstages[c];
-        ar.chunk[c] = ar.nunits[c] >= 96 * 32 ? 96 : ar.nunits[c] >= 256 ? 8 : 1;
-        const int64_t per = 8LL * ar.chunk[c];
-        ar.wg0[c + 1] = ar.wg0[c] + (ar.nunits[c] + per - 1) / per * per;
-    }
-    if (ar.wg0[kDgClasses] > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    if (tb.lds_bytes > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void*)direct_backward_kernel,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, tb.lds_bytes);
+    // classes 0 and 1 in one launch, class 2 in its own with more LDS
+    for (int c0 = 0; c0 < kDgClasses; c0 += 2) {
+        ar.ncls = c0 == 0 ? 2 : 1;
+        ar.wg0[0] = 0;
+        int lds = 0;
+        for (int i = 0; i < ar.ncls; ++i) {
+            const int c = c0 + i, P = dg_pairs(dg_groups(c));
+            ar.G[i] = dg_groups(c);
+            ar.stage0[i] = 0;
+            for (int k = 0; k < c; ++k) ar.stage0[i] += tb.nstages[k];
+            ar.nunits[i] = (N + P - 1) / P * tb.nstages[c];
+            ar.chunk[i] = ar.nunits[i] >= 96 * 32 ? 96 : ar.nunits[i] >= 256 ? 8 : 1;
+            const int64_t per = 8LL * ar.chunk[i];
+            ar.wg0[i + 1] = ar.wg0[i] + (ar.nunits[i] + per - 1) / per * per;
+            lds = std::max(lds, tb.lds_bytes[c]);
+        }
+        const int64_t grid = ar.wg0[ar.ncls];
+        if (grid == 0) continue;
+        if (grid > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
+        if (lds > 64 * 1024) {
+            const hipError_t e = hipFuncSetAttribute((const void*)direct_backward_kernel,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return (int)e;
+        }
+        hipLaunchKernelGGL(direct_backward_kernel, dim3((unsigned)grid), dim3(kDgThreads), lds, (hipStream_t)stream, ar);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL(direct_backward_kernel, dim3((unsigned)ar.wg0[kDgClasses]), dim3(kDgThreads), tb.lds_bytes,
-                       (hipStream_t)stream, ar);
-    const int err = (int)hipGetLastError();
-    return err ? err : launch_backward_sums(ws, gx1, gx2, N, L, stream);
+    return launch_backward_sums(ws, gx1, gx2, N, L, stream);
 }
 
 }  // namespace cgtp

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "cgtp_direct.h"
+#include "cgtp_internal.h"
 
 namespace cgtp {
 
@@ -212,22 +213,16 @@ void dir_build(int L, DirHost<T>& h) {
 struct DgHost {
     std::vector<float> coef;
     std::vector<DgTask> tasks;
-    std::vector<DgBlock> blocks;
+    std::vector<DgOut> outs;
+    std::vector<DgPart> parts;
     std::vector<DgStage> stages;
     int nstages[kDgClasses] = {0, 0, 0};
-    int lds_bytes = 0;
+    int lds_bytes[kDgClasses] = {0, 0, 0};
 };
-
-// Class of a block: the fewest groups of orders (least work on orders a block
-// does not have) whose run of gradients stays near 32 KiB per work-group.
-inline int dg_class(int l1, int l2) {
-    const int sz = (2 * l1 + 1) * (2 * l2 + 1);
-    return sz <= 512 ? 0 : sz <= 1100 ? 1 : 2;
-}
 
 // The gradient kernel's table and work lists of degree L.
 inline void dg_build(int L, DgHost& h) {
-    const int max_lds = 52 * 1024;   // stages of several blocks: three work-groups per CU
+    const int max_lds_of[kDgClasses] = {52 * 1024, 52 * 1024, 79 * 1024};   // three, three, two work-groups per CU
     std::vector<std::vector<double>> cg;
     std::map<std::pair<int, int>, std::vector<int>> first;   // (la, lb) -> first chunk of each task
     for (int la = 0; la <= L; ++la)
@@ -270,26 +265,28 @@ inline void dg_build(int L, DgHost& h) {
     std::vector<Cost> by_class[kDgClasses];
     for (int b0 = 0; b0 < nblk;) {
         const int cls = dg_class(b0 / (L + 1), b0 % (L + 1)), G = dg_groups(cls), P = dg_pairs(G), RS = dg_row(G);
+        const int max_lds = max_lds_of[cls];
         DgStage st{};
         st.off = boff[b0];
         st.l1a = st.l1b = b0 / (L + 1);
         st.l2a = st.l2b = b0 % (L + 1);
-        int b1 = b0, acc_rows = 0;
+        int b1 = b0, acc_rows = 0, len = 0;
         auto tile = [&](int l1b, int l2a, int l2b) {
             return (dg_tile_row(l1b + 1, st.l1a) + dg_tile_row(l2b + 1, l2a)) * RS;
         };
-        auto lds = [&](int tile_len, int len, int rows) {
-            return 4 * (((tile_len + P * (len | 1) + 7) & ~3) + rows * 2 * P);
+        auto lds = [&](int tile_len, int n, int rows) {
+            return 4 * (((tile_len + 3) & ~3) + P * dir_run<float>(n) + rows * RS + 4);
         };
         while (b1 < nblk) {
             const int l1 = b1 / (L + 1), l2 = b1 % (L + 1), la = std::min(l1, l2), lb = std::max(l1, l2);
             if (dg_class(l1, l2) != cls) break;
             const int nrg = (2 * la + 4) / 4, nt = (nrg + kDgRows - 1) / kDgRows;
             const int rows = 4 * nrg + nt * (2 * lb + 2);
-            const int len = st.len + (2 * l1 + 1) * (2 * l2 + 1);
+            const int n = len + (2 * l1 + 1) * (2 * l2 + 1);
             const int l1b = std::max(st.l1b, l1), l2a = std::min(st.l2a, l2), l2b = std::max(st.l2b, l2);
-            if (b1 > b0 && lds(tile(l1b, l2a, l2b), len, acc_rows + rows) > max_lds) break;
-            st.len = len;
+            const int reads = (l1b + 1) * (l1b + 1) - st.l1a * st.l1a + (l2b + 1) * (l2b + 1) - l2a * l2a;
+            if (b1 > b0 && (lds(tile(l1b, l2a, l2b), n, acc_rows + rows) > max_lds || reads > kDgMaxInputs)) break;
+            len = n;
             st.l1b = l1b;
             st.l2a = l2a;
             st.l2b = l2b;
@@ -298,11 +295,36 @@ inline void dg_build(int L, DgHost& h) {
         }
         st.x2tile = dg_tile_row(st.l1b + 1, st.l1a) * RS;
         st.tile_len = (tile(st.l1b, st.l2a, st.l2b) + 3) & ~3;
-        st.acc0 = (st.tile_len + P * (st.len | 1) + 3) & ~3;
-        st.acc_len = acc_rows * 2 * P;
-        h.lds_bytes = std::max(h.lds_bytes, 4 * (st.acc0 + st.acc_len));
+        // parts: one, or for a single large block as many as it takes to keep to the
+        // LDS of the class (their steps start at whole chunks)
+        st.part0 = (int)h.parts.size();
+        int run = 0;
+        if (b1 > b0 + 1) {
+            h.parts.push_back({st.off, len, 0, 4 * L + 4});
+            run = dir_run<float>(len);
+        } else {
+            const int l1 = st.l1a, l2 = st.l2a, lt = l1 + l2, d = std::abs(l1 - l2), n = lt - d + 1, KC = dg_kc(G);
+            int np = 1, per = n;
+            for (;; ++np) {
+                per = ((n + np - 1) / np + KC - 1) / KC * KC;
+                run = 0;
+                for (int s0 = 0; s0 < n; s0 += per) {
+                    const int hi = lt - s0, lo = std::max(d, hi - per + 1);
+                    run = std::max(run, dir_run<float>((hi + 1) * (hi + 1) - lo * lo));
+                }
+                if (per <= KC || 4 * (st.tile_len + P * run + acc_rows * RS + 4) <= max_lds) break;
+            }
+            for (int s0 = 0; s0 < n; s0 += per) {
+                const int hi = lt - s0, lo = std::max(d, hi - per + 1);
+                h.parts.push_back({st.off + lo * lo - d * d, (hi + 1) * (hi + 1) - lo * lo, s0, s0 + hi - lo + 1});
+            }
+        }
+        st.nparts = (int)h.parts.size() - st.part0;
+        st.acc0 = st.tile_len + P * run;
+        st.acc_len = (acc_rows * RS + 3) & ~3;
+        h.lds_bytes[cls] = std::max(h.lds_bytes[cls], 4 * (st.acc0 + st.acc_len));
         st.task0 = (int)h.tasks.size();
-        st.block0 = (int)h.blocks.size();
+        st.out0 = (int)h.outs.size();
         int64_t cost = 0;
         int acc = st.acc0;
         for (int b = b0; b < b1; ++b) {
@@ -310,15 +332,25 @@ inline void dg_build(int L, DgHost& h) {
             const bool swap = l1 > l2;
             const int t1 = dg_tile_row(l1, st.l1a) * RS, t2 = st.x2tile + dg_tile_row(l2, st.l2a) * RS;
             const int nrg = (2 * la + 4) / 4, nt = (nrg + kDgRows - 1) / kDgRows;
-            const int stride = (2 * lb + 2) * 2 * P;
-            DgBlock bl{};
-            bl.l1 = l1;
-            bl.l2 = l2;
-            bl.acca = acc;
-            bl.accb = acc + 4 * nrg * 2 * P;
-            bl.ntasks = nt;
-            bl.stride = stride;
-            h.blocks.push_back(bl);
+            const int stride = (2 * lb + 2) * RS, accb = acc + 4 * nrg * RS;
+            const int n1 = 2 * l1 + 1, n2 = 2 * l2 + 1;
+            for (int e = 0; e < n1 + n2; ++e) {
+                const bool first_in = e < n1;
+                const int l = first_in ? l1 : l2, m = (first_in ? e : e - n1) - l;
+                DgOut o{};
+                if (first_in != swap) {   // the smaller degree's input (x1 if equal)
+                    o.plus = acc + (l - m) * RS;
+                    o.minus = acc + (l + m) * RS + P;
+                    o.code = 1;
+                } else {
+                    o.plus = accb + (l + m) * RS;
+                    o.minus = accb + (l - m) * RS + P;
+                    o.code = nt | stride << 4;
+                }
+                o.code |= e << 20;
+                o.ws = (int)bwd_block_off(L, l1, l2) | (n1 + n2) << 20;
+                h.outs.push_back(o);
+            }
             for (int t = 0; t < nt; ++t) {
                 DgTask k{};
                 const int k0 = 4 * kDgRows * t, rgs = std::min(kDgRows, nrg - kDgRows * t);
@@ -328,18 +360,18 @@ inline void dg_build(int L, DgHost& h) {
                 k.xb = swap ? t1 : t2;
                 const int d = lb - la;
                 k.goff = boff[b] - st.off - d * d;
-                k.acca = bl.acca + k0 * 2 * P;
-                k.accb = bl.accb + t * stride;
+                k.acca = acc + k0 * RS;
+                k.accb = accb + t * stride;
                 h.tasks.push_back(k);
                 for (int m0 = 0; m0 <= la + lb; m0 += dg_orders(G)) {
                     const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
                     if (nk > k0) cost += (int64_t)rgs * nk + 8;
                 }
             }
-            acc = bl.accb + nt * stride;
+            acc = accb + nt * stride;
         }
         st.ntasks = (int)h.tasks.size() - st.task0;
-        st.nblocks = b1 - b0;
+        st.nouts = (int)h.outs.size() - st.out0;
         std::stable_sort(h.tasks.begin() + st.task0, h.tasks.end(), [](const DgTask& x, const DgTask& y) {
             auto w = [](const DgTask& t) {   // rows x steps of the first orders, as a measure
                 const int la = t.code & 255, lb = t.code >> 8 & 255;

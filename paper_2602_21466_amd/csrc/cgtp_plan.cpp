@@ -900,8 +900,8 @@ int upload_direct(cgtp_plan_s* p, cgtp::DirTables<T>* tb) {
         size_t bytes, off;
     };
     auto part = [](const auto& v) { return Part{v.data(), v.size() * sizeof(v[0]), 0}; };
-    Part parts[8] = {part(h.coef), part(h.items), part(h.stages), part(h.groups),
-                     part(d.coef), part(d.tasks), part(d.blocks), part(d.stages)};
+    Part parts[9] = {part(h.coef), part(h.items), part(h.stages), part(h.groups), part(d.coef),
+                     part(d.tasks), part(d.outs), part(d.parts), part(d.stages)};
     size_t total = 0;
     for (auto& q : parts) {
         q.off = total;
@@ -937,10 +937,13 @@ int upload_direct(cgtp_plan_s* p, cgtp::DirTables<T>* tb) {
     tb->lds_bytes = h.lds_bytes;
     p->dg.coef = (const float*)(base + parts[4].off);
     p->dg.tasks = (const cgtp::DgTask*)(base + parts[5].off);
-    p->dg.blocks = (const cgtp::DgBlock*)(base + parts[6].off);
-    p->dg.stages = (const cgtp::DgStage*)(base + parts[7].off);
-    for (int c = 0; c < cgtp::kDgClasses; ++c) p->dg.nstages[c] = d.nstages[c];
-    p->dg.lds_bytes = d.lds_bytes;
+    p->dg.outs = (const cgtp::DgOut*)(base + parts[6].off);
+    p->dg.parts = (const cgtp::DgPart*)(base + parts[7].off);
+    p->dg.stages = (const cgtp::DgStage*)(base + parts[8].off);
+    for (int c = 0; c < cgtp::kDgClasses; ++c) {
+        p->dg.nstages[c] = d.nstages[c];
+        p->dg.lds_bytes[c] = d.lds_bytes[c];
+    }
     return CGTP_OK;
 }
 

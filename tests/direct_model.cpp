@@ -117,9 +117,10 @@ static double backward(int L) {
         for (int i = 0; i < h.nstages[cls]; ++i, ++si) {
             const DgStage& st = h.stages[(size_t)si];
             const int G = dg_groups(cls), P = dg_pairs(G), RS = dg_row(G), HM = dg_orders(G), KC = dg_kc(G);
-            need(4 * (st.acc0 + st.acc_len) <= h.lds_bytes, "stage larger than the LDS of the launch");
-            need(st.tile_len + P * (st.len | 1) <= st.acc0, "run overlaps the sums");
-            covered += st.len;
+            need(4 * (st.acc0 + st.acc_len) <= h.lds_bytes[cls] && st.acc0 % 4 == 0 && st.acc_len % 4 == 0,
+                 "stage larger than the LDS of the launch");
+            need((st.l1b + 1) * (st.l1b + 1) - st.l1a * st.l1a + (st.l2b + 1) * (st.l2b + 1) - st.l2a * st.l2a <= kDgMaxInputs,
+                 "more inputs than the threads of a pair hold");
             std::vector<double> tile[2];
             for (int s = 0; s < 2; ++s) {
                 tile[s].assign((size_t)st.tile_len, 0.0);
@@ -134,59 +135,64 @@ static double backward(int L) {
             std::vector<double> sums[2];   // by sign of the order; element / (2 P) is the row
             for (auto& v : sums) v.assign((size_t)st.acc_len, 0.0);
             auto at = [&](int s, int e) -> double& {
-                need(e >= st.acc0 && e + 2 * P <= st.acc0 + st.acc_len, "sum outside the sums");
+                need(e >= st.acc0 && e + P <= st.acc0 + st.acc_len, "sum outside the sums");
                 return sums[s][(size_t)(e - st.acc0)];
             };
-            for (int ti = st.task0; ti < st.task0 + st.ntasks; ++ti) {
-                const DgTask& t = h.tasks[(size_t)ti];
-                const int la = t.code & 255, lb = t.code >> 8 & 255, k0 = t.code >> 16 & 255, rgs = t.code >> 24 & 15;
-                const int swap = t.code >> 28 & 1, lt = la + lb;
-                size_t ck = (size_t)t.chunk0;
-                for (int m0 = 0; m0 <= lt; m0 += HM) {
-                    const int nk = std::min(2 * la + 1, lt - m0 + 1);
-                    if (nk <= k0) break;
-                    for (int s = 0; s < 2; ++s)
-                        for (int o = 0; o < HM; ++o)
-                            for (int r = 0; r < 4 * rgs; ++r) {
-                                double T = 0;
-                                for (int k = 0; k < nk; ++k) {
-                                    const size_t ci = (ck + (size_t)(k / KC) * rgs + r / 4) * kDirChunk +
-                                                      (size_t)dg_coef_index(G, k % KC, o, r % 4);
-                                    need(ci < h.coef.size(), "read past the coefficients");
-                                    const int l3 = lt - k, M = m0 + o;
-                                    if (M > l3 || (s && !M)) continue;
-                                    const int q = t.goff + l3 * (l3 + 1) + (s ? -M : M);
-                                    need(q >= 0 && q < st.len, "gradient read outside the run");
-                                    T += ((k & 1) && s != swap ? -1.0 : 1.0) * (double)h.coef[ci] * g[(size_t)(st.off + q)];
+            for (int pi = st.part0; pi < st.part0 + st.nparts; ++pi) {
+                const DgPart& part = h.parts[(size_t)pi];
+                need(st.tile_len + P * dir_run<float>(part.len) <= st.acc0, "run overlaps the sums");
+                need(part.s0 % KC == 0, "a part starts inside a chunk");
+                covered += part.len;
+                for (int ti = st.task0; ti < st.task0 + st.ntasks; ++ti) {
+                    const DgTask& t = h.tasks[(size_t)ti];
+                    const int la = t.code & 255, lb = t.code >> 8 & 255, k0 = t.code >> 16 & 255, rgs = t.code >> 24 & 15;
+                    const int swap = t.code >> 28 & 1, lt = la + lb;
+                    size_t ck = (size_t)t.chunk0;
+                    for (int m0 = 0; m0 <= lt; m0 += HM) {
+                        const int nk = std::min(2 * la + 1, lt - m0 + 1), s1 = std::min(nk, part.s1);
+                        if (nk <= k0 || nk <= part.s0) break;
+                        for (int s = 0; s < 2; ++s)
+                            for (int o = 0; o < HM; ++o)
+                                for (int r = 0; r < 4 * rgs; ++r) {
+                                    double T = 0;
+                                    for (int k = part.s0; k < s1; ++k) {
+                                        const size_t ci = (ck + (size_t)(k / KC) * rgs + r / 4) * kDirChunk +
+                                                          (size_t)dg_coef_index(G, k % KC, o, r % 4);
+                                        need(ci < h.coef.size(), "read past the coefficients");
+                                        const int l3 = lt - k, M = m0 + o;
+                                        if (M > l3 || (s && !M)) continue;
+                                        const int q = t.goff + l3 * (l3 + 1) + (s ? -M : M) - (part.off - st.off);
+                                        need(q >= 0 && q < part.len, "gradient read outside the run");
+                                        T += ((k & 1) && s != swap ? -1.0 : 1.0) * (double)h.coef[ci] *
+                                             g[(size_t)(part.off + q)];
+                                    }
+                                    const int d = std::min(lb - la + k0 + m0 + o + r, 2 * lb + 1);
+                                    const int ea = t.xa - r * RS, eb = t.xb + d * RS;
+                                    need(ea >= 0 && ea + 2 * P <= st.tile_len && eb >= 0 && eb + 2 * P <= st.tile_len,
+                                         "read past the tiles");
+                                    if (m0 + o > lt) need(T == 0, "order past the block");
+                                    at(s, t.acca + r * RS + s * P) += T * tile[s][(size_t)eb];
+                                    at(s, t.accb + d * RS + s * P) += T * tile[s][(size_t)ea];
                                 }
-                                const int d = std::min(lb - la + k0 + m0 + o + r, 2 * lb + 1);
-                                const int ea = t.xa - r * RS, eb = t.xb + d * RS;
-                                need(ea >= 0 && ea + 2 * P <= st.tile_len && eb >= 0 && eb + 2 * P <= st.tile_len,
-                                     "read past the tiles");
-                                if (m0 + o > lt) need(T == 0, "order past the block");
-                                at(s, t.acca + r * 2 * P) += T * tile[s][(size_t)eb];
-                                at(s, t.accb + d * 2 * P) += T * tile[s][(size_t)ea];
-                            }
-                    ck += (size_t)((nk + KC - 1) / KC * rgs);
-                }
-                need((ck + (size_t)rgs) * kDirChunk <= h.coef.size(), "read ahead past the coefficients");
-            }
-            for (int b = st.block0; b < st.block0 + st.nblocks; ++b) {
-                const DgBlock& bl = h.blocks[(size_t)b];
-                const bool swap = bl.l1 > bl.l2;
-                for (int in = 0; in < 2; ++in) {
-                    const int l = in ? bl.l2 : bl.l1;
-                    for (int m = -l; m <= l; ++m) {
-                        double v = 0;
-                        if ((in == 0) != swap)
-                            v = at(0, bl.acca + (l - m) * 2 * P) + at(1, bl.acca + (l + m) * 2 * P);
-                        else
-                            for (int t = 0; t < bl.ntasks; ++t)
-                                v += at(0, bl.accb + t * bl.stride + (l + m) * 2 * P) +
-                                     at(1, bl.accb + t * bl.stride + (l - m) * 2 * P);
-                        grad[in][(size_t)(l * l + l + m)] += v;
+                        ck += (size_t)((nk + KC - 1) / KC * rgs);
+                        need((ck + (size_t)rgs) * kDirChunk <= h.coef.size(), "read ahead past the coefficients");
                     }
                 }
+            }
+            for (int oi = st.out0; oi < st.out0 + st.nouts; ++oi) {
+                const DgOut& o = h.outs[(size_t)oi];
+                const int nt = o.code & 15, stride = o.code >> 4 & 0xffff, e = o.code >> 20, nrow = o.ws >> 20;
+                double v = 0;
+                for (int t = 0; t < nt; ++t) v += at(0, o.plus + t * stride) + at(1, o.minus + t * stride);
+                // the block from its place in the workspace
+                int l1 = 0, l2 = 0;
+                while ((int)bwd_block_off(L, l1, l2) != (o.ws & 0xfffff))
+                    if (++l2 > L) l2 = 0, need(++l1 <= L, "no such block");
+                need(nrow == 2 * (l1 + l2 + 1) && e < nrow, "wrong component");
+                if (e < 2 * l1 + 1)
+                    grad[0][(size_t)(l1 * l1 + e)] += v;
+                else
+                    grad[1][(size_t)(l2 * l2 + e - (2 * l1 + 1))] += v;
             }
         }
     need(covered == nout, "stages do not cover the outputs");

@@ -77,7 +77,7 @@ def test_forward_and_real_match_oracle(L, N, dtype):
     plan.close()
 
 
-# ragged tiles of 16, 8 and 4 pairs (the three classes of blocks: largest degrees up to 11, 16 and above)
+# ragged tiles of 16 and 8 pairs; the three classes of blocks (largest degrees up to 6, 16 and above)
 @pytest.mark.gpu
 @pytest.mark.parametrize("L,N", [(0, 1), (1, 17), (3, 15), (6, 33), (11, 16), (13, 9), (16, 8), (18, 5)])
 def test_gradients_match_oracle(L, N):
