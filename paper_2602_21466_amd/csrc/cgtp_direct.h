@@ -1,5 +1,6 @@
 // Internal layout of the direct contraction, shared by its plan
-// (cgtp_direct_plan.cpp) and its kernels (cgtp_direct.hip).  Not part of the
+// (cgtp_direct_plan.h) and its kernels (cgtp_direct.hip,
+// cgtp_direct_backward.hip).  Not part of the
 // public ABI.
 //
 // Every (l1, l2) block of the CGTP is, per order M >= 0 of the output, one
@@ -10,8 +11,7 @@
 // -M use the same matrix on the reversed products, up to the sign
 // (-1)^(l1+l2-l3), and block (lb, la) the same up to that sign.  Per block that
 // is 2 n^2 multiply-adds per M for 2 n outputs: at L = 32 31 M per pair, a
-// fifth of the arithmetic of the sphere-grid method, all of it on the matrix
-// cores, and the outputs are then bound by the memory they are written to.
+// fifth of the arithmetic of the sphere-grid method, all of it contraction.
 #pragma once
 
 #include <hip/hip_runtime.h>
