@@ -195,6 +195,20 @@ struct DgTables {
 
 template <typename T> struct ChanArgs;
 
+// HIP takes fewer than 2^32 work-items per launch, so a launch of many pairs at
+// a low degree goes out in several: calls launch(first work-group, work-groups)
+// until `total` work-groups, in rounds of `per`, are covered or a launch fails.
+template <typename F>
+int dir_launches(int64_t total, int64_t per, int threads, F&& launch) {
+    const int64_t most = 0xffffffffLL / threads / per * per;
+    for (int64_t first = 0; first < total; first += most) {
+        const int64_t left = (total - first + per - 1) / per * per;
+        const int err = launch(first, (unsigned)(left < most ? left : most));
+        if (err) return err;
+    }
+    return 0;
+}
+
 // Weak, so that the plan's host code also links without the device code (it
 // never calls them then: no table can be uploaded).
 __attribute__((weak)) int launch_direct_f32(const DirTables<float>& tb, const float* x1, const float* x2, float* out, int64_t N, int L,

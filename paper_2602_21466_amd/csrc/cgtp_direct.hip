@@ -50,6 +50,7 @@ struct DirArgs {
     int64_t N;
     int64_t ntiles;     // tiles of pairs
     int64_t nunits;     // groups x tiles
+    int64_t unit0;      // first unit of the launch
     int32_t chunk;      // consecutive units given to one XCD
     int32_t L;
     int32_t channels, flags, npaths;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(kDirThreads, 4) void direct_kernel(const DirArgs<T>
     // read the same coefficients share its L2
     const int64_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     const int64_t ck = j / ar.chunk;
-    const int64_t unit = (ck * 8 + xcd) * ar.chunk + (j - ck * ar.chunk);
+    const int64_t unit = ar.unit0 + (ck * 8 + xcd) * ar.chunk + (j - ck * ar.chunk);
     if (unit >= ar.nunits) return;
     const int64_t gi = unit / ar.ntiles;
     const int64_t p0 = (unit - gi * ar.ntiles) * P;
@@ -277,14 +278,18 @@ __global__ __launch_bounds__(kDirThreads, 4) void direct_kernel(const DirArgs<T>
 }
 
 template <typename T, int MODE>
-int launch_mode(const DirTables<T>& tb, const DirArgs<T>& ar, unsigned grid, void* stream) {
+int launch_mode(const DirTables<T>& tb, DirArgs<T>& ar, void* stream) {
     const void* kern = (const void*)direct_kernel<T, MODE>;
     if (tb.lds_bytes > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, tb.lds_bytes);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL((direct_kernel<T, MODE>), dim3(grid), dim3(kDirThreads), tb.lds_bytes, (hipStream_t)stream, ar);
-    return (int)hipGetLastError();
+    return dir_launches(ar.nunits, 8LL * ar.chunk, kDirThreads, [&](int64_t first, unsigned grid) {
+        ar.unit0 = first;
+        hipLaunchKernelGGL((direct_kernel<T, MODE>), dim3(grid), dim3(kDirThreads), tb.lds_bytes, (hipStream_t)stream,
+                           ar);
+        return (int)hipGetLastError();
+    });
 }
 
 template <typename T>
@@ -300,22 +305,18 @@ int launch(const DirTables<T>& tb, const T* x1, const T* x2, T* out, int64_t N, 
     ar.out = out;
     ar.N = N;
     ar.ntiles = (N + dir_pairs<T>() - 1) / dir_pairs<T>();
-    if (ar.ntiles > 0x7fffffffLL / tb.ngroups) return (int)hipErrorInvalidConfiguration;
     ar.nunits = ar.ntiles * tb.ngroups;
     // 64 units at a time (the work-groups an XCD runs at once) where every XCD
     // gets several such chunks, else fewer
     ar.chunk = (int32_t)(ar.nunits >= 64 * 32 ? 64 : ar.nunits >= 256 ? 8 : 1);
-    const int64_t per = 8LL * ar.chunk;
-    const int64_t grid = (ar.nunits + per - 1) / per * per;
-    if (grid > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     ar.L = L;
-    if (real_basis) return launch_mode<T, kDirReal>(tb, ar, (unsigned)grid, stream);
-    if (!ch) return launch_mode<T, kDirPlain>(tb, ar, (unsigned)grid, stream);
+    if (real_basis) return launch_mode<T, kDirReal>(tb, ar, stream);
+    if (!ch) return launch_mode<T, kDirPlain>(tb, ar, stream);
     ar.w = ch->w;
     ar.channels = ch->channels;
     ar.flags = ch->flags;
     ar.npaths = ch->npaths;
-    return launch_mode<T, kDirWeighted>(tb, ar, (unsigned)grid, stream);
+    return launch_mode<T, kDirWeighted>(tb, ar, stream);
 }
 
 }  // namespace

@@ -45,6 +45,7 @@ struct DgArgs {
     int32_t G[2], stage0[2];
     int64_t nunits[2];       // stages x tiles of pairs
     int64_t wg0[3];          // first work-group of each class
+    int64_t first;           // and of the launch
     int32_t chunk[2];        // consecutive units given to one XCD
     int32_t L;
 };
@@ -286,9 +287,10 @@ __device__ __forceinline__ void dg_stage(const DgArgs& ar, const DgStage& st, in
 __global__ __launch_bounds__(kDgThreads, 3) void direct_backward_kernel(const DgArgs ar) {
     extern __shared__ __align__(16) unsigned char dg_smem[];
     float* smem = reinterpret_cast<float*>(dg_smem);
-    const int c = ar.ncls > 1 && (int64_t)blockIdx.x >= ar.wg0[1] ? 1 : 0;
+    const int64_t wg = ar.first + blockIdx.x;
+    const int c = ar.ncls > 1 && wg >= ar.wg0[1] ? 1 : 0;
     // (work-groups of a class start at a multiple of 8: work-group i runs on XCD i mod 8)
-    const int64_t i = blockIdx.x - ar.wg0[c], xcd = i & 7, j = i >> 3, ck = j / ar.chunk[c];
+    const int64_t i = wg - ar.wg0[c], xcd = i & 7, j = i >> 3, ck = j / ar.chunk[c];
     const int64_t unit = (ck * 8 + xcd) * ar.chunk[c] + (j - ck * ar.chunk[c]);
     if (unit >= ar.nunits[c]) return;
     const int P = dg_pairs(ar.G[c]);
@@ -333,17 +335,18 @@ int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2,
             ar.wg0[i + 1] = ar.wg0[i] + (ar.nunits[i] + per - 1) / per * per;
             lds = std::max(lds, tb.lds_bytes[c]);
         }
-        const int64_t grid = ar.wg0[ar.ncls];
-        if (grid == 0) continue;
-        if (grid > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
+        if (ar.wg0[ar.ncls] == 0) continue;
         if (lds > 64 * 1024) {
             const hipError_t e = hipFuncSetAttribute((const void*)direct_backward_kernel,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return (int)e;
         }
-        hipLaunchKernelGGL(direct_backward_kernel, dim3((unsigned)grid), dim3(kDgThreads), lds, (hipStream_t)stream, ar);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return (int)e;
+        const int err = dir_launches(ar.wg0[ar.ncls], 8, kDgThreads, [&](int64_t first, unsigned grid) {
+            ar.first = first;
+            hipLaunchKernelGGL(direct_backward_kernel, dim3(grid), dim3(kDgThreads), lds, (hipStream_t)stream, ar);
+            return (int)hipGetLastError();
+        });
+        if (err) return err;
     }
     return launch_backward_sums(ws, gx1, gx2, N, L, stream);
 }

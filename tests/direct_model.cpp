@@ -2,7 +2,7 @@
 // every item of every group as the kernel does, with every index checked
 // against its buffer, and compares the outputs with the plain double sum over
 // the oracle's Racah-formula coefficients.
-//   usage: direct_model fp32|fp64|backward|cg L
+//   usage: direct_model fp32|fp64|backward|cg|launches L
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -234,10 +234,33 @@ static double coefficients(int L) {
     return worst;
 }
 
+// Launches of a call of about 2^L work-groups: below 2^32 work-items each, whole
+// rounds, every work-group once.  Returns how many there are.
+static double launches(int L) {
+    int n = 0;
+    for (int64_t total : {((int64_t)1 << L) - 1, (int64_t)1 << L, ((int64_t)1 << L) + 5})
+        for (int threads : {256, 512})
+            for (int64_t per : {8, 64, 512}) {
+                int64_t next = 0;
+                n = 0;
+                const int err = dir_launches(total, per, threads, [&](int64_t first, unsigned grid) {
+                    need(first == next && first % per == 0 && grid > 0 && grid % per == 0, "not whole rounds in order");
+                    need((uint64_t)grid * (uint64_t)threads < ((uint64_t)1 << 32), "too many work-items in a launch");
+                    next = first + grid;
+                    ++n;
+                    return 0;
+                });
+                need(err == 0 && next >= total && next < total + per, "work-groups left out");
+                need(dir_launches(total, per, threads, [&](int64_t, unsigned) { return 7; }) == 7, "a failure is lost");
+            }
+    return n;
+}
+
 int main(int argc, char** argv) {
-    need(argc == 3, "usage: direct_model fp32|fp64|backward|cg L");
+    need(argc == 3, "usage: direct_model fp32|fp64|backward|cg|launches L");
     const int L = std::atoi(argv[2]);
     const bool fp64 = !std::strcmp(argv[1], "fp64"), bwd = !std::strcmp(argv[1], "backward");
+    if (!std::strcmp(argv[1], "launches")) return std::printf("%.17g\n", launches(L)), 0;
     const double e = !std::strcmp(argv[1], "cg") ? coefficients(L) : bwd ? backward(L) : fp64 ? run<double>(L) : run<float>(L);
     std::printf("%.17g\n", e);
     return 0;

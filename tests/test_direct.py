@@ -47,6 +47,12 @@ def test_work_lists_cover_every_output_once(model, dtype, L):
     assert model(dtype, L) < TOL.get(dtype, 1e-6)
 
 
+# one launch takes fewer than 2^32 work-items: 2^23 - 1 work-groups of 512 threads
+@pytest.mark.parametrize("L,n", [(1, 1), (9, 1), (23, 2), (26, 9), (31, 257)])
+def test_launches_cover_every_work_group(model, L, n):
+    assert model("launches", L) == n
+
+
 def _rel(a, b):
     return float(np.linalg.norm(a - b) / np.linalg.norm(b))
 
@@ -139,4 +145,24 @@ def test_infinite_input_stays_in_its_blocks():
             o = lib.cgtp_path_offset(L, l1, l2, abs(l1 - l2))
             keep[n, o:o + (2 * l1 + 1) * (2 * l2 + 1)] = False
         assert torch.equal(z[keep], ref[keep])
+    plan.close()
+
+
+@pytest.mark.gpu
+def test_more_pairs_than_one_launch_takes():
+    """Degree 0 (outputs x1 x2, exact): pairs past the work-items of one launch, 16 pairs per work-group of 512
+    (forward) and 256 (gradients) threads."""
+    import torch
+    import paper_2602_21466_amd as lib
+    plan = lib.Plan(0)
+    n = 2 ** 27 + 17
+    print("case L=0 N=%d forward" % n, flush=True)
+    x1, x2 = (torch.randn(n, 1, device="cuda") for _ in range(2))
+    assert torch.equal(plan.forward(x1, x2), x1 * x2)
+    assert torch.equal(plan.forward_real(x1, x2), x1 * x2)
+    n = 2 ** 28 + 17
+    print("case L=0 N=%d gradients" % n, flush=True)
+    x1, x2, g = (torch.randn(n, 1, device="cuda") for _ in range(3))
+    g1, g2 = plan.backward(x1, x2, g)
+    assert torch.equal(g1, g * x2) and torch.equal(g2, g * x1)
     plan.close()
