@@ -80,15 +80,30 @@ struct DirGroup {
     int32_t tile_len;    // elements of both tiles, a multiple of 4
 };
 
+// One way to cut the outputs into groups.  The long list's groups share the
+// filling of their input tiles over several stages; the short list's are one
+// short stage each, for calls whose pairs give the long list too few work-groups
+// to fill the chip, so that each is a long chain of stages.  The items are the
+// same, so the outputs do not depend on the list, to the last bit.
+struct DirList {
+    int32_t group0, ngroups;
+    int32_t lds_bytes;
+};
+
 template <typename T>
 struct DirTables {
     const T* coef;
     const DirItem* items;
     const DirStage* stages;
     const DirGroup* groups;
-    int32_t ngroups;
-    int32_t lds_bytes;
+    DirList lists[2];   // long, short
 };
+// The short list is taken while it makes at most six work-groups per CU.  (us, long
+// list / short: fp64 L = 4, 1 pair 18.7 / 7.7; L = 6, 1000 39.8 / 24.4 (800
+// work-groups); L = 19, 16 103 / 46 (1229); L = 10, 300 49 / 32 (1560); above: L = 8,
+// 1000 40 / 68 (2304).  fp32 L = 8, 16 19.6 / 7.9; L = 20, 1 24.4 / 9.1 (1060); real
+// L = 13, 100 29 / 17 (1540); L = 8, 1000 23.3 / 24.4 (2205); L = 11, 300 20 / 25 (2223).)
+constexpr int64_t kDirShortMax = 6 * 256;
 
 // fp32 coefficients of a chunk: element (lane, mi) at 4 lane + mi with
 // lane = ((group of orders) kc + k) 4 + row; fp64: (k, mi, row) at 16 k + 4 mi + row.
@@ -183,15 +198,28 @@ struct alignas(16) DgStage {
     int32_t pad;
 };
 
+// One way to cut the blocks into stages (by class): the long list's stages fill
+// the LDS of their class, the short list's hold one block, or small ones together.
+// A block's tasks and parts are the same in both, and so are the gradients.
+struct DgList {
+    int32_t stage0;
+    int32_t nstages[kDgClasses];
+    int32_t lds_bytes[kDgClasses];
+};
+
 struct DgTables {
     const float* coef;
     const DgTask* tasks;
     const DgOut* outs;
     const DgPart* parts;
-    const DgStage* stages;       // by class
-    int32_t nstages[kDgClasses];
-    int32_t lds_bytes[kDgClasses];
+    const DgStage* stages;
+    DgList lists[2];             // long, short
 };
+// The short list is taken while it makes at most two work-groups per CU.  (us, long
+// list / short: L = 3, 16 pairs 16.8 / 14.1; L = 4, 300 20.3 / 16.9 (228
+// work-groups); L = 5, 300 19.7 / 17.5 (380); above: L = 13, 48 24.3 / 26.8 (753);
+// L = 3, 3000 18.6 / 22.8 (940).)
+constexpr int64_t kDgShortMax = 2 * 256;
 
 template <typename T> struct ChanArgs;
 

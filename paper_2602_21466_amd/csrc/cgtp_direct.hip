@@ -278,15 +278,15 @@ __global__ __launch_bounds__(kDirThreads, 4) void direct_kernel(const DirArgs<T>
 }
 
 template <typename T, int MODE>
-int launch_mode(const DirTables<T>& tb, DirArgs<T>& ar, void* stream) {
+int launch_mode(int lds_bytes, DirArgs<T>& ar, void* stream) {
     const void* kern = (const void*)direct_kernel<T, MODE>;
-    if (tb.lds_bytes > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, tb.lds_bytes);
+    if (lds_bytes > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (e != hipSuccess) return (int)e;
     }
     return dir_launches(ar.nunits, 8LL * ar.chunk, kDirThreads, [&](int64_t first, unsigned grid) {
         ar.unit0 = first;
-        hipLaunchKernelGGL((direct_kernel<T, MODE>), dim3(grid), dim3(kDirThreads), tb.lds_bytes, (hipStream_t)stream,
+        hipLaunchKernelGGL((direct_kernel<T, MODE>), dim3(grid), dim3(kDirThreads), lds_bytes, (hipStream_t)stream,
                            ar);
         return (int)hipGetLastError();
     });
@@ -299,24 +299,25 @@ int launch(const DirTables<T>& tb, const T* x1, const T* x2, T* out, int64_t N, 
     ar.coef = tb.coef;
     ar.items = tb.items;
     ar.stages = tb.stages;
-    ar.groups = tb.groups;
     ar.x1 = x1;
     ar.x2 = x2;
     ar.out = out;
     ar.N = N;
     ar.ntiles = (N + dir_pairs<T>() - 1) / dir_pairs<T>();
-    ar.nunits = ar.ntiles * tb.ngroups;
+    const DirList& ls = tb.lists[ar.ntiles * tb.lists[1].ngroups <= kDirShortMax ? 1 : 0];
+    ar.groups = tb.groups + ls.group0;
+    ar.nunits = ar.ntiles * ls.ngroups;
     // 64 units at a time (the work-groups an XCD runs at once) where every XCD
     // gets several such chunks, else fewer
     ar.chunk = (int32_t)(ar.nunits >= 64 * 32 ? 64 : ar.nunits >= 256 ? 8 : 1);
     ar.L = L;
-    if (real_basis) return launch_mode<T, kDirReal>(tb, ar, stream);
-    if (!ch) return launch_mode<T, kDirPlain>(tb, ar, stream);
+    if (real_basis) return launch_mode<T, kDirReal>(ls.lds_bytes, ar, stream);
+    if (!ch) return launch_mode<T, kDirPlain>(ls.lds_bytes, ar, stream);
     ar.w = ch->w;
     ar.channels = ch->channels;
     ar.flags = ch->flags;
     ar.npaths = ch->npaths;
-    return launch_mode<T, kDirWeighted>(tb, ar, stream);
+    return launch_mode<T, kDirWeighted>(ls.lds_bytes, ar, stream);
 }
 
 }  // namespace

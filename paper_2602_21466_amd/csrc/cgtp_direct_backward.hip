@@ -319,6 +319,12 @@ int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2,
     ar.ws = ws;
     ar.N = N;
     ar.L = L;
+    int64_t units = 0;
+    for (int c = 0; c < kDgClasses; ++c) {
+        const int P = dg_pairs(dg_groups(c));
+        units += (N + P - 1) / P * tb.lists[1].nstages[c];
+    }
+    const DgList& ls = tb.lists[units <= kDgShortMax ? 1 : 0];
     // classes 0 and 1 in one launch, class 2 in its own with more LDS
     for (int c0 = 0; c0 < kDgClasses; c0 += 2) {
         ar.ncls = c0 == 0 ? 2 : 1;
@@ -327,13 +333,13 @@ int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2,
         for (int i = 0; i < ar.ncls; ++i) {
             const int c = c0 + i, P = dg_pairs(dg_groups(c));
             ar.G[i] = dg_groups(c);
-            ar.stage0[i] = 0;
-            for (int k = 0; k < c; ++k) ar.stage0[i] += tb.nstages[k];
-            ar.nunits[i] = (N + P - 1) / P * tb.nstages[c];
+            ar.stage0[i] = ls.stage0;
+            for (int k = 0; k < c; ++k) ar.stage0[i] += ls.nstages[k];
+            ar.nunits[i] = (N + P - 1) / P * ls.nstages[c];
             ar.chunk[i] = ar.nunits[i] >= 96 * 32 ? 96 : ar.nunits[i] >= 256 ? 8 : 1;
             const int64_t per = 8LL * ar.chunk[i];
             ar.wg0[i + 1] = ar.wg0[i] + (ar.nunits[i] + per - 1) / per * per;
-            lds = std::max(lds, tb.lds_bytes[c]);
+            lds = std::max(lds, ls.lds_bytes[c]);
         }
         if (ar.wg0[ar.ncls] == 0) continue;
         if (lds > 64 * 1024) {

@@ -20,7 +20,7 @@ struct DirHost {
     std::vector<DirItem> items;
     std::vector<DirStage> stages;
     std::vector<DirGroup> groups;
-    int lds_bytes = 0;
+    DirList lists[2] = {};   // long, short
 };
 
 // For fixed (la, lb, M) the coefficients of l3 are the eigenvector of
@@ -79,48 +79,15 @@ inline void dir_cg_block(int la, int lb, std::vector<std::vector<double>>& out) 
     }
 }
 
-// The coefficient table and the work lists of degree L.
+// First coefficient chunk of each (row group, first order) of the blocks la <= lb.
+using DirFirst = std::map<std::pair<int, int>, std::vector<std::vector<int>>>;
+
+// One list of groups: stages of up to max_len outputs per pair; a group takes
+// blocks together up to group_len outputs, or with `split` is a single stage.
 template <typename T>
-void dir_build(int L, DirHost<T>& h) {
-    constexpr int P = dir_pairs<T>(), KC = dir_kc<T>(), HM = dir_orders<T>();
-    // a stage's run, per pair: up to 40 KiB (fp32) of LDS for the pairs of a
-    // work-group, so that two work-groups share a CU; four degrees of the
-    // largest block always fit
-    const int max_len = std::max(40 * 1024 / (P * 4) - 1, 8 * L - 8);
-    // a group takes blocks together until one filling of the input tiles serves
-    // about four stages' worth of outputs (two stages: 1147 us instead of 1105 at
-    // L = 16, N = 8192; 164 instead of 155 in the real basis at L = 11, N = 4001;
-    // one stage 1211 and 185), with tiles of at most 24 KiB (fp32)
-    const int group_len = 4 * max_len, max_tile = sizeof(T) == 4 ? 6144 : 7680;
-
-    // coefficients of the blocks la <= lb: first chunk of (row group, orders m0..)
-    std::map<std::pair<int, int>, std::vector<std::vector<int>>> first;
-    std::vector<std::vector<double>> cg;
-    for (int la = 0; la <= L; ++la)
-        for (int lb = la; lb <= L; ++lb) {
-            dir_cg_block(la, lb, cg);
-            auto& f = first[{la, lb}];
-            f.resize((size_t)(2 * la + 1 + kDirRows - 1) / kDirRows);
-            for (int rg = 0; rg < (int)f.size(); ++rg) {
-                const int lt = la + lb - kDirRows * rg;
-                for (int m0 = 0; m0 <= lt; m0 += HM) {
-                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
-                    const int nch = (nk + KC - 1) / KC;
-                    const size_t at = h.coef.size();
-                    f[(size_t)rg].push_back((int)(at / kDirChunk));
-                    h.coef.resize(at + (size_t)nch * kDirChunk, (T)0);
-                    for (int o = 0; o < HM && m0 + o <= lt; ++o) {
-                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
-                        const auto& a = cg[(size_t)(m0 + o)];
-                        for (int r = 0; r < kDirRows && kDirRows * rg + r < n; ++r)
-                            for (int k = 0; k < n; ++k)
-                                h.coef[at + (size_t)(k / KC) * kDirChunk + dir_coef_index<T>(k % KC, o, r)] =
-                                    (T)a[(size_t)(kDirRows * rg + r) * n + k];
-                    }
-                }
-            }
-        }
-
+void dir_list(int L, const DirFirst& first, int max_len, int group_len, bool split, DirHost<T>& h, DirList& list) {
+    constexpr int P = dir_pairs<T>(), HM = dir_orders<T>();
+    const int max_tile = sizeof(T) == 4 ? 6144 : 7680;   // elements: 24 KiB (fp32)
     struct Piece {   // one row group of one block, in output order
         int l1, l2, rg, off, len;
     };
@@ -172,6 +139,7 @@ void dir_build(int L, DirHost<T>& h) {
         }
         int64_t cost = 0;
         for (size_t i = 0; i < pieces.size();) {
+            if (split) cost = 0;
             DirStage st{(int)h.items.size(), 0, pieces[i].off, 0};
             size_t j = i;
             for (; j < pieces.size() && (j == i || st.len + pieces[j].len <= max_len); ++j) {
@@ -182,7 +150,7 @@ void dir_build(int L, DirHost<T>& h) {
                 const int b = q.l1 * (L + 1) + q.l2, lt = q.l1 + q.l2 - kDirRows * q.rg;
                 const int t1 = dir_tile_row<T>(q.l1, g.l1a) * dir_row<T>();
                 const int t2 = g.x2tile + dir_tile_row<T>(q.l2, g.l2a) * dir_row<T>();
-                const auto& f = first[{la, lb}][(size_t)q.rg];
+                const auto& f = first.at({la, lb})[(size_t)q.rg];
                 for (int m0 = 0; m0 <= lt; m0 += HM) {
                     DirItem it{};
                     it.chunk0 = f[(size_t)(m0 / HM)];
@@ -202,14 +170,63 @@ void dir_build(int L, DirHost<T>& h) {
             lds = std::max(lds, ((size_t)g.tile_len + (size_t)P * (st.len | 1)) * sizeof(T));
             h.stages.push_back(st);
             i = j;
+            if (split || i == pieces.size()) {
+                g.nstages = (int)h.stages.size() - g.stage0;
+                groups.push_back({g, cost});
+                g.stage0 += g.nstages;
+            }
         }
-        g.nstages = (int)h.stages.size() - g.stage0;
-        groups.push_back({g, cost});
         b0 = b1;
     }
     std::stable_sort(groups.begin(), groups.end(), [](const Cost& x, const Cost& y) { return x.cost > y.cost; });
+    list = {(int)h.groups.size(), (int)groups.size(), (int)lds};
     for (const auto& c : groups) h.groups.push_back(c.g);
-    h.lds_bytes = (int)lds;
+}
+
+// The coefficient table and the work lists of degree L.
+template <typename T>
+void dir_build(int L, DirHost<T>& h) {
+    constexpr int KC = dir_kc<T>(), HM = dir_orders<T>();
+    // coefficients of the blocks la <= lb: first chunk of (row group, orders m0..)
+    DirFirst first;
+    std::vector<std::vector<double>> cg;
+    for (int la = 0; la <= L; ++la)
+        for (int lb = la; lb <= L; ++lb) {
+            dir_cg_block(la, lb, cg);
+            auto& f = first[{la, lb}];
+            f.resize((size_t)(2 * la + 1 + kDirRows - 1) / kDirRows);
+            for (int rg = 0; rg < (int)f.size(); ++rg) {
+                const int lt = la + lb - kDirRows * rg;
+                for (int m0 = 0; m0 <= lt; m0 += HM) {
+                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
+                    const int nch = (nk + KC - 1) / KC;
+                    const size_t at = h.coef.size();
+                    f[(size_t)rg].push_back((int)(at / kDirChunk));
+                    h.coef.resize(at + (size_t)nch * kDirChunk, (T)0);
+                    for (int o = 0; o < HM && m0 + o <= lt; ++o) {
+                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
+                        const auto& a = cg[(size_t)(m0 + o)];
+                        for (int r = 0; r < kDirRows && kDirRows * rg + r < n; ++r)
+                            for (int k = 0; k < n; ++k)
+                                h.coef[at + (size_t)(k / KC) * kDirChunk + dir_coef_index<T>(k % KC, o, r)] =
+                                    (T)a[(size_t)(kDirRows * rg + r) * n + k];
+                    }
+                }
+            }
+        }
+    // long: a stage's run, per pair, takes up to 40 KiB (fp32) of LDS for the pairs
+    // of a work-group, so that two work-groups share a CU; four degrees of the
+    // largest block always fit.  A group takes blocks together until one filling of
+    // the input tiles serves about four stages' worth of outputs (two stages: 1147 us
+    // instead of 1105 at L = 16, N = 8192; 164 instead of 155 in the real basis at
+    // L = 11, N = 4001; one stage 1211 and 185)
+    const int max_len = std::max(40 * 1024 / (dir_pairs<T>() * 4) - 1, 8 * L - 8);
+    dir_list<T>(L, first, max_len, 4 * max_len, false, h, h.lists[0]);
+    // short: single stages of 256 (fp64: 128) outputs where that many are more than
+    // four degrees of a block (half as many: 12.0 instead of 9.4 us in the real basis
+    // at L = 16, N = 16; twice as many: 11.0 instead of 7.8 in fp64 at L = 4, N = 100)
+    const int short_len = 4096 / dir_pairs<T>();
+    dir_list<T>(L, first, short_len, short_len, true, h, h.lists[1]);
 }
 
 struct DgHost {
@@ -218,41 +235,14 @@ struct DgHost {
     std::vector<DgOut> outs;
     std::vector<DgPart> parts;
     std::vector<DgStage> stages;
-    int nstages[kDgClasses] = {0, 0, 0};
-    int lds_bytes[kDgClasses] = {0, 0, 0};
+    DgList lists[2] = {};   // long, short
 };
 
-// The gradient kernel's table and work lists of degree L.
-inline void dg_build(int L, DgHost& h) {
+using DgFirst = std::map<std::pair<int, int>, std::vector<int>>;   // (la, lb) -> first chunk of each task
+
+// One list of stages; several blocks share a stage up to max_len outputs.
+inline void dg_list(int L, const DgFirst& first, int max_len, DgHost& h, DgList& list) {
     const int max_lds_of[kDgClasses] = {52 * 1024, 52 * 1024, 79 * 1024};   // three, three, two work-groups per CU
-    std::vector<std::vector<double>> cg;
-    std::map<std::pair<int, int>, std::vector<int>> first;   // (la, lb) -> first chunk of each task
-    for (int la = 0; la <= L; ++la)
-        for (int lb = la; lb <= L; ++lb) {
-            dir_cg_block(la, lb, cg);
-            const int G = dg_groups(dg_class(la, lb)), HM = dg_orders(G), KC = dg_kc(G);
-            const int nrg = (2 * la + 1 + 3) / 4;
-            for (int rg0 = 0; rg0 < nrg; rg0 += kDgRows) {
-                const int rgs = std::min(kDgRows, nrg - rg0);
-                first[{la, lb}].push_back((int)(h.coef.size() / kDirChunk));
-                for (int m0 = 0; m0 <= la + lb; m0 += HM) {
-                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
-                    if (nk <= 4 * rg0) break;
-                    const int nch = (nk + KC - 1) / KC;
-                    const size_t at = h.coef.size();
-                    h.coef.resize(at + (size_t)nch * rgs * kDirChunk, 0.0f);
-                    for (int o = 0; o < HM && m0 + o <= la + lb; ++o) {
-                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
-                        const auto& a = cg[(size_t)(m0 + o)];
-                        for (int s = 0; s < n; ++s)
-                            for (int r = 0; r < 4 * rgs && 4 * rg0 + r < n; ++r)
-                                h.coef[at + ((size_t)(s / KC) * rgs + r / 4) * kDirChunk +
-                                       dg_coef_index(G, s % KC, o, r % 4)] = (float)a[(size_t)s * n + 4 * rg0 + r];
-                    }
-                }
-            }
-        }
-    h.coef.resize(h.coef.size() + (size_t)kDgRows * kDirChunk, 0.0f);   // read ahead of the last chunk
     const int nblk = (L + 1) * (L + 1);
     std::vector<int> boff(nblk);
     for (int b = 0, off = 0; b < nblk; ++b) {
@@ -287,7 +277,9 @@ inline void dg_build(int L, DgHost& h) {
             const int n = len + (2 * l1 + 1) * (2 * l2 + 1);
             const int l1b = std::max(st.l1b, l1), l2a = std::min(st.l2a, l2), l2b = std::max(st.l2b, l2);
             const int reads = (l1b + 1) * (l1b + 1) - st.l1a * st.l1a + (l2b + 1) * (l2b + 1) - l2a * l2a;
-            if (b1 > b0 && (lds(tile(l1b, l2a, l2b), n, acc_rows + rows) > max_lds || reads > kDgMaxInputs)) break;
+            if (b1 > b0 && (n > max_len || lds(tile(l1b, l2a, l2b), n, acc_rows + rows) > max_lds ||
+                            reads > kDgMaxInputs))
+                break;
             len = n;
             st.l1b = l1b;
             st.l2a = l2a;
@@ -324,7 +316,7 @@ inline void dg_build(int L, DgHost& h) {
         st.nparts = (int)h.parts.size() - st.part0;
         st.acc0 = st.tile_len + P * run;
         st.acc_len = (acc_rows * RS + 3) & ~3;
-        h.lds_bytes[cls] = std::max(h.lds_bytes[cls], 4 * (st.acc0 + st.acc_len));
+        list.lds_bytes[cls] = std::max(list.lds_bytes[cls], 4 * (st.acc0 + st.acc_len));
         st.task0 = (int)h.tasks.size();
         st.out0 = (int)h.outs.size();
         int64_t cost = 0;
@@ -356,7 +348,7 @@ inline void dg_build(int L, DgHost& h) {
             for (int t = 0; t < nt; ++t) {
                 DgTask k{};
                 const int k0 = 4 * kDgRows * t, rgs = std::min(kDgRows, nrg - kDgRows * t);
-                k.chunk0 = first[{la, lb}][(size_t)t];
+                k.chunk0 = first.at({la, lb})[(size_t)t];
                 k.code = la | lb << 8 | k0 << 16 | rgs << 24 | (swap ? 1 << 28 : 0);
                 k.xa = (swap ? t2 : t1) + (2 * la - k0) * RS;
                 k.xb = swap ? t1 : t2;
@@ -384,11 +376,47 @@ inline void dg_build(int L, DgHost& h) {
         by_class[cls].push_back({st, cost});
         b0 = b1;
     }
+    list.stage0 = (int)h.stages.size();
     for (int c = 0; c < kDgClasses; ++c) {
         std::stable_sort(by_class[c].begin(), by_class[c].end(), [](const Cost& x, const Cost& y) { return x.cost > y.cost; });
         for (const auto& s : by_class[c]) h.stages.push_back(s.s);
-        h.nstages[c] = (int)by_class[c].size();
+        list.nstages[c] = (int)by_class[c].size();
     }
+}
+
+// The gradient kernel's table and work lists of degree L.
+inline void dg_build(int L, DgHost& h) {
+    std::vector<std::vector<double>> cg;
+    DgFirst first;
+    for (int la = 0; la <= L; ++la)
+        for (int lb = la; lb <= L; ++lb) {
+            dir_cg_block(la, lb, cg);
+            const int G = dg_groups(dg_class(la, lb)), HM = dg_orders(G), KC = dg_kc(G);
+            const int nrg = (2 * la + 1 + 3) / 4;
+            for (int rg0 = 0; rg0 < nrg; rg0 += kDgRows) {
+                const int rgs = std::min(kDgRows, nrg - rg0);
+                first[{la, lb}].push_back((int)(h.coef.size() / kDirChunk));
+                for (int m0 = 0; m0 <= la + lb; m0 += HM) {
+                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
+                    if (nk <= 4 * rg0) break;
+                    const int nch = (nk + KC - 1) / KC;
+                    const size_t at = h.coef.size();
+                    h.coef.resize(at + (size_t)nch * rgs * kDirChunk, 0.0f);
+                    for (int o = 0; o < HM && m0 + o <= la + lb; ++o) {
+                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
+                        const auto& a = cg[(size_t)(m0 + o)];
+                        for (int s = 0; s < n; ++s)
+                            for (int r = 0; r < 4 * rgs && 4 * rg0 + r < n; ++r)
+                                h.coef[at + ((size_t)(s / KC) * rgs + r / 4) * kDirChunk +
+                                       dg_coef_index(G, s % KC, o, r % 4)] = (float)a[(size_t)s * n + 4 * rg0 + r];
+                    }
+                }
+            }
+        }
+    h.coef.resize(h.coef.size() + (size_t)kDgRows * kDirChunk, 0.0f);   // read ahead of the last chunk
+    dg_list(L, first, INT32_MAX, h, h.lists[0]);
+    // (128 outputs: 16.5 instead of 14.3 us at L = 3, N = 100)
+    dg_list(L, first, 64, h, h.lists[1]);
 }
 
 }  // namespace cgtp

@@ -938,17 +938,13 @@ int upload_direct(cgtp_plan_s* p, cgtp::DirTables<T>* tb) {
     tb->items = (const cgtp::DirItem*)(base + parts[1].off);
     tb->stages = (const cgtp::DirStage*)(base + parts[2].off);
     tb->groups = (const cgtp::DirGroup*)(base + parts[3].off);
-    tb->ngroups = (int32_t)h.groups.size();
-    tb->lds_bytes = h.lds_bytes;
+    for (int i = 0; i < 2; ++i) tb->lists[i] = h.lists[i];
     p->dg.coef = (const float*)(base + parts[4].off);
     p->dg.tasks = (const cgtp::DgTask*)(base + parts[5].off);
     p->dg.outs = (const cgtp::DgOut*)(base + parts[6].off);
     p->dg.parts = (const cgtp::DgPart*)(base + parts[7].off);
     p->dg.stages = (const cgtp::DgStage*)(base + parts[8].off);
-    for (int c = 0; c < cgtp::kDgClasses; ++c) {
-        p->dg.nstages[c] = d.nstages[c];
-        p->dg.lds_bytes[c] = d.lds_bytes[c];
-    }
+    for (int i = 0; i < 2; ++i) p->dg.lists[i] = d.lists[i];
     return CGTP_OK;
 }
 

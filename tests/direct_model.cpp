@@ -22,9 +22,7 @@ static void need(bool ok, const char* what) {
 }
 
 template <typename T>
-static double run(int L) {
-    DirHost<T> h;
-    dir_build<T>(L, h);
+static double run(int L, const DirHost<T>& h, const DirList& list) {
     constexpr int HM = dir_orders<T>(), KC = dir_kc<T>(), RS = dir_row<T>();
     const int nin = (L + 1) * (L + 1), nout = nin * nin;
     std::vector<double> x[2], out(nout, NAN);
@@ -32,7 +30,8 @@ static double run(int L) {
         r.resize(nin);
         for (auto& v : r) v = drand48() - 0.5;
     }
-    for (const auto& g : h.groups) {
+    for (int gi = list.group0; gi < list.group0 + list.ngroups; ++gi) {
+        const DirGroup& g = h.groups[(size_t)gi];
         std::vector<double> tile[2];   // orders as given and reversed
         for (int s = 0; s < 2; ++s) {
             tile[s].assign((size_t)g.tile_len, 0.0);
@@ -50,7 +49,7 @@ static double run(int L) {
         for (int si = g.stage0; si < g.stage0 + g.nstages; ++si) {
             const DirStage& st = h.stages[(size_t)si];
             std::vector<double> buf((size_t)st.len, NAN);
-            need(((size_t)g.tile_len + (size_t)dir_pairs<T>() * (st.len | 1)) * sizeof(T) <= (size_t)h.lds_bytes,
+            need(((size_t)g.tile_len + (size_t)dir_pairs<T>() * (st.len | 1)) * sizeof(T) <= (size_t)list.lds_bytes,
                  "stage larger than the LDS of the launch");
             for (int ii = st.item0; ii < st.item0 + st.nitems; ++ii) {
                 const DirItem& it = h.items[(size_t)ii];
@@ -99,10 +98,20 @@ static double run(int L) {
     return std::sqrt(num / den);
 }
 
+// Both lists of the plan; the outputs of one seed are the same to the last bit.
+template <typename T>
+static double forward(int L) {
+    DirHost<T> h;
+    dir_build<T>(L, h);
+    srand48(1);
+    const double e = run<T>(L, h, h.lists[0]);
+    srand48(1);
+    need(run<T>(L, h, h.lists[1]) == e, "the lists differ");
+    return e;
+}
+
 // The gradient kernel's lists (fp32), run task by task in the same way.
-static double backward(int L) {
-    DgHost h;
-    dg_build(L, h);
+static double backward(int L, const DgHost& h, const DgList& list) {
     const int nin = (L + 1) * (L + 1), nout = nin * nin;
     std::vector<double> x[2], grad[2], ref[2], g(nout);
     for (int i = 0; i < 2; ++i) {
@@ -112,12 +121,12 @@ static double backward(int L) {
         for (auto& v : x[i]) v = drand48() - 0.5;
     }
     for (auto& v : g) v = drand48() - 0.5;
-    int si = 0, covered = 0;
+    int si = list.stage0, covered = 0;
     for (int cls = 0; cls < kDgClasses; ++cls)
-        for (int i = 0; i < h.nstages[cls]; ++i, ++si) {
+        for (int i = 0; i < list.nstages[cls]; ++i, ++si) {
             const DgStage& st = h.stages[(size_t)si];
             const int G = dg_groups(cls), P = dg_pairs(G), RS = dg_row(G), HM = dg_orders(G), KC = dg_kc(G);
-            need(4 * (st.acc0 + st.acc_len) <= h.lds_bytes[cls] && st.acc0 % 4 == 0 && st.acc_len % 4 == 0,
+            need(4 * (st.acc0 + st.acc_len) <= list.lds_bytes[cls] && st.acc0 % 4 == 0 && st.acc_len % 4 == 0,
                  "stage larger than the LDS of the launch");
             need((st.l1b + 1) * (st.l1b + 1) - st.l1a * st.l1a + (st.l2b + 1) * (st.l2b + 1) - st.l2a * st.l2a <= kDgMaxInputs,
                  "more inputs than the threads of a pair hold");
@@ -216,6 +225,15 @@ static double backward(int L) {
     return std::sqrt(num / den);
 }
 
+static double gradients(int L) {
+    DgHost h;
+    dg_build(L, h);
+    srand48(1);
+    const double a = backward(L, h, h.lists[0]);
+    srand48(1);
+    return std::max(a, backward(L, h, h.lists[1]));
+}
+
 // Largest error of the plan's coefficients against the oracle's.
 static double coefficients(int L) {
     double worst = 0;
@@ -261,7 +279,7 @@ int main(int argc, char** argv) {
     const int L = std::atoi(argv[2]);
     const bool fp64 = !std::strcmp(argv[1], "fp64"), bwd = !std::strcmp(argv[1], "backward");
     if (!std::strcmp(argv[1], "launches")) return std::printf("%.17g\n", launches(L)), 0;
-    const double e = !std::strcmp(argv[1], "cg") ? coefficients(L) : bwd ? backward(L) : fp64 ? run<double>(L) : run<float>(L);
+    const double e = !std::strcmp(argv[1], "cg") ? coefficients(L) : bwd ? gradients(L) : fp64 ? forward<double>(L) : forward<float>(L);
     std::printf("%.17g\n", e);
     return 0;
 }

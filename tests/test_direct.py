@@ -103,6 +103,32 @@ def test_gradients_match_oracle(L, N):
     plan.close()
 
 
+# one tile of pairs and a few, which take the short lists of groups and stages, against
+# more pairs than those are taken for
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,N,dtype", [(2, 25000, "fp32"), (5, 4500, "fp32"), (8, 900, "fp32"), (13, 200, "fp32"),
+                                       (19, 40, "fp32"), (3, 17000, "fp64"), (6, 2100, "fp64"), (12, 260, "fp64")])
+def test_outputs_do_not_depend_on_the_number_of_pairs(L, N, dtype):
+    import torch
+    import paper_2602_21466_amd as lib
+    print("case L=%d N=%d %s" % (L, N, dtype), flush=True)
+    nin = (L + 1) ** 2
+    x1, x2 = _rows(torch, N, nin, dtype, L).cuda(), _rows(torch, N, nin, dtype, 100 + L).cuda()
+    w = _rows(torch, N, lib.cgtp_num_paths(L), dtype, 200 + L).cuda()
+    g = _rows(torch, N, nin ** 2, dtype, 300 + L).cuda() if dtype == "fp32" else None
+    plan = lib.Plan(L, dtype=dtype)
+
+    def calls(n):
+        z = [plan.forward(x1[:n], x2[:n]), plan.forward_real(x1[:n], x2[:n]),
+             plan.forward_weighted(x1[:n, None].contiguous(), x2[:n], w[:n, None].contiguous())[:, 0]]
+        return z + list(plan.backward(x1[:n], x2[:n], g[:n]) if g is not None else ())
+    many = calls(N)
+    for n in (1, 17):
+        for a, b in zip(calls(n), many):
+            assert torch.equal(a, b[:n])
+    plan.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shared,weights", [(True, "channel"), (False, "pair"), (True, "none")])
 def test_routes_agree(shared, weights):
