@@ -11,9 +11,9 @@
 // or three work-groups per CU overlap only in part: of 2692 us at L = 16, 8192
 // pairs (an earlier version), 1469 were left without the tasks, 1998 without the
 // loads of the gradient, 768 without both; the sums take 135.  Measured (us,
-// sphere-grid kernels before / now): L = 16, 8192 pairs 33102 / 2407; L = 32, 1024
-// pairs 53600 / 5009.  grad_b by LDS float atomics 4107 at L = 16, by ordered
-// plain reads and writes 2707.
+// sphere-grid kernels before / now): L = 16, 4000 pairs 16150 / 1055; L = 32, 226
+// pairs 11889 / 1115.  grad_b by LDS float atomics 4107 at L = 16, 8192 pairs, by
+// ordered plain reads and writes 2707.
 
 #include <hip/hip_runtime.h>
 
@@ -44,8 +44,7 @@ struct DgArgs {
     int32_t ncls;
     int32_t G[2], stage0[2];
     int64_t nunits[2];       // stages x tiles of pairs
-    int64_t wg0[3];          // first work-group of each class
-    int64_t first;           // and of the launch
+    int64_t wg0[3];          // first work-group of each class, counted from the launch's first
     int32_t chunk[2];        // consecutive units given to one XCD
     int32_t L;
 };
@@ -189,40 +188,40 @@ __device__ __forceinline__ void dg_stage(const DgArgs& ar, const DgStage& st, in
     const int nin = (ar.L + 1) * (ar.L + 1);
     const int64_t nout = (int64_t)nin * nin;
     float* run = smem + st.tile_len;
-    // the run of a part, 16 bytes at a time: it starts as far from a 16-byte boundary
-    // in LDS as in memory
+    constexpr int TP = kDgThreads / P;   // threads per pair that load its inputs and runs
+    const int xp = tid / TP, xi = tid & (TP - 1);
+    // the run of a part, 16 bytes at a time, eight loads in flight per thread: it starts
+    // as far from a 16-byte boundary in LDS as in memory.  (Threads of its own for each
+    // pair; with the waves taking the pairs in turn L = 4, 16 pairs took 15.8 us instead
+    // of 14.3, L = 16, 4000 pairs 1207 instead of 1055; four loads in flight 1091.)
+    constexpr int kLoads = 8;
     auto load_run = [&](const DgPart& part, int ps) {
-        for (int p = wave; p < np; p += kDgWaves) {
-            const int64_t o = (p0 + p) * nout + part.off;
-            const int sh = (int)(o & 3), end = sh + part.len;
-            const float* src = ar.g + (o - sh);
-            float* dst = run + p * ps;
-            for (int i0 = 4 * lane; i0 < end; i0 += 4 * 256) {   // four loads in flight per lane
-                f32x4 v[4];
+        const int64_t o = (p0 + xp) * nout + part.off;
+        const int sh = (int)(o & 3), end = xp < np ? sh + part.len : 0;
+        const float* src = ar.g + (o - sh);
+        float* dst = run + xp * ps;
+        const int full = end & ~3, e = full + xi;   // (the last elements one by one)
+        const float last = e < end ? src[e] : 0.0f;
+        for (int i0 = 4 * xi; i0 < full; i0 += 4 * kLoads * TP) {
+            f32x4 v[kLoads];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = i0 + 256 * u;
-                    if (i + 4 <= end)
-                        v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + i));
-                    else {
+            for (int u = 0; u < kLoads; ++u) {
+                const int i = i0 + 4 * TP * u;
+                if (i < full) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + i));
+            }
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) v[u][q] = i + q < end ? src[i + q] : 0.0f;
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = i0 + 256 * u;
-                    if (i < end) *reinterpret_cast<f32x4*>(dst + i) = v[u];
-                }
+            for (int u = 0; u < kLoads; ++u) {
+                const int i = i0 + 4 * TP * u;
+                if (i < full) *reinterpret_cast<f32x4*>(dst + i) = v[u];
             }
         }
+        if (e < end) dst[e] = last;
     };
-    // ---- input tiles (TP threads per pair, all of a thread's loads in flight), zero
-    // rows around the degrees, cleared sums
+    // ---- input tiles (all of a thread's loads in flight), zero rows around the
+    // degrees, cleared sums
     {
-        constexpr int TP = kDgThreads / P, kX = (kDgMaxInputs + TP - 1) / TP;
+        constexpr int kX = (kDgMaxInputs + TP - 1) / TP;
         const int e1 = (st.l1b + 1) * (st.l1b + 1) - st.l1a * st.l1a, e2 = (st.l2b + 1) * (st.l2b + 1) - st.l2a * st.l2a;
-        const int xp = tid / TP, xi = tid & (TP - 1);
         const int64_t row = p0 + xp < ar.N ? p0 + xp : ar.N - 1;   // (columns past N are not written out)
         const float* r1 = ar.x1 + row * nin + st.l1a * st.l1a;
         const float* r2 = ar.x2 + row * nin + st.l2a * st.l2a - e1;
@@ -287,10 +286,9 @@ __device__ __forceinline__ void dg_stage(const DgArgs& ar, const DgStage& st, in
 __global__ __launch_bounds__(kDgThreads, 3) void direct_backward_kernel(const DgArgs ar) {
     extern __shared__ __align__(16) unsigned char dg_smem[];
     float* smem = reinterpret_cast<float*>(dg_smem);
-    const int64_t wg = ar.first + blockIdx.x;
-    const int c = ar.ncls > 1 && wg >= ar.wg0[1] ? 1 : 0;
+    const int c = ar.ncls > 1 && (int64_t)blockIdx.x >= ar.wg0[1] ? 1 : 0;
     // (work-groups of a class start at a multiple of 8: work-group i runs on XCD i mod 8)
-    const int64_t i = wg - ar.wg0[c], xcd = i & 7, j = i >> 3, ck = j / ar.chunk[c];
+    const int64_t i = blockIdx.x - ar.wg0[c], xcd = i & 7, j = i >> 3, ck = j / ar.chunk[c];
     const int64_t unit = (ck * 8 + xcd) * ar.chunk[c] + (j - ck * ar.chunk[c]);
     if (unit >= ar.nunits[c]) return;
     const int P = dg_pairs(ar.G[c]);
@@ -348,8 +346,9 @@ int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2,
             if (e != hipSuccess) return (int)e;
         }
         const int err = dir_launches(ar.wg0[ar.ncls], 8, kDgThreads, [&](int64_t first, unsigned grid) {
-            ar.first = first;
-            hipLaunchKernelGGL(direct_backward_kernel, dim3(grid), dim3(kDgThreads), lds, (hipStream_t)stream, ar);
+            DgArgs al = ar;
+            for (int i = 0; i <= ar.ncls; ++i) al.wg0[i] -= first;
+            hipLaunchKernelGGL(direct_backward_kernel, dim3(grid), dim3(kDgThreads), lds, (hipStream_t)stream, al);
             return (int)hipGetLastError();
         });
         if (err) return err;
