@@ -370,7 +370,6 @@ struct cgtp_plan_s {
     // caller chose is what they get.  fp64 gradients stay on the sphere-grid
     // kernels: the direct ones are written for the fp32 matrix instruction only.
     bool direct = false;
-    void* dmem_dir = nullptr;
     cgtp::DirTables<float> df{};
     cgtp::DirTables<double> dd{};
     cgtp::DgTables dg{};       // its gradients (fp32)
@@ -424,9 +423,10 @@ template <typename T>
 int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std::vector<int32_t>& list) {
     const int L = p->L;
     const cgtp_grid& g = p->grid;
-    // fp32 plans of the direct contraction take only the facts about the method
-    // (grids, K, flops, which gradients exist) from here, not its tables
-    const bool tables = !p->direct || sizeof(T) == 8;
+    // plans of the direct contraction take only the facts about the method (grids,
+    // K, flops, which gradients exist) from here, and in fp64 the gradient kernels'
+    // tables
+    const bool tables = !p->direct || sizeof(T) == 8, forward = !p->direct;
     // ---- grids: one Legendre table per distinct node count
     std::map<int, int> grid_lmax;          // n_theta -> largest degree needed
     std::map<int, int> grid_lmax_out;
@@ -604,7 +604,7 @@ int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std:
             if (!tables) continue;
             // MFMA tiles in the order the waves take them: by |m|, row tile, column tile
             b.tdesc_off = (int)h.tdesc.size();
-            {
+            if (forward) {
                 cgtp::TileGeom geo{(b.J - b.d) / 2 + 1, ncomp, pairs};
                 for (int mp = 0; mp <= b.J; ++mp)
                     for (int rt = 0; rt < geo.nrt(mp, b.d); ++rt)
@@ -704,13 +704,13 @@ int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std:
                 // multiplied by i on odd paths and read in the real basis: r_0 =
                 // Re z_0, r_mu = sqrt 2 Re z_-mu, r_-mu = sqrt 2 Im z_-mu.
                 const size_t nr0 = h.coefr.size();
-                if (!cross) {
+                if (forward && !cross) {
                     for (size_t k = b.coef_off * (size_t)4; k < h.coef.size(); k += 4) {
                         h.coefr.insert(h.coefr.end(), {h.coef[k], (T)0, (T)0, (T)0});
                         const int32_t e0 = h.coefi[k];
                         h.coefir.insert(h.coefir.end(), {e0, e0, e0, e0});
                     }
-                } else {
+                } else if (forward) {
                     const long double sc_r = 2.0L * kPi / b.Phi;   // exact unpacking: no factor 1/4
                     const long double sr_e = sc_r * ((b.products & cgtp::kEvenDot) ? cg_vec(1, 1, -1, 0, 0) : 1.0L);
                     const long double sr_v = sc_r * ((b.products & cgtp::kOddSV) ? 1.0L : cg_vec(1, 1, 0, 1, 1));
@@ -786,11 +786,12 @@ int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std:
                         }
                     }
                 }
-                if (h.coefr.size() - nr0 != h.coef.size() - (size_t)b.coef_off * 4) return CGTP_EUNSUP;
+                if (forward && h.coefr.size() - nr0 != h.coef.size() - (size_t)b.coef_off * 4) return CGTP_EUNSUP;
             }
             p->lds_bytes = std::max(p->lds_bytes, b.lds_bytes);
             blocks.push_back(b);
         }
+    if (!forward) h.coefi.clear();
     p->min_abs_K = min_abs_K;
     double lflops = 0;
     for (const auto& kv : lifts) lflops += lift_flops(kv.first[1], kv.second[0], kv.second[1], kv.second[2]);
@@ -832,119 +833,85 @@ int build(cgtp_plan_s* p, std::vector<BlockDesc>& blocks, HostTables<T>& h, std:
     return CGTP_OK;
 }
 
-template <typename T>
-int upload(cgtp_plan_s* p, const std::vector<BlockDesc>& blocks, const HostTables<T>& h,
-           const std::vector<int32_t>& list, cgtp::Tables<T>* tb) {
-    const std::vector<T>* parts[] = {&h.pbar, &h.wtab, &h.tw, &h.lcg, &h.coef, &h.coefr};
-    constexpr int kParts = 6;
-    size_t offs[kParts + 2];
-    size_t total = 0;
-    for (int i = 0; i < kParts; ++i) {
-        offs[i] = total;
-        total = align_up(total + parts[i]->size() * sizeof(T), 256);
-    }
-    offs[kParts] = total;
-    total = align_up(total + blocks.size() * sizeof(BlockDesc), 256);
-    offs[kParts + 1] = total;
-    total = align_up(total + list.size() * sizeof(int32_t), 256);
-    const size_t tdesc_off = total;
-    total = align_up(total + h.tdesc.size() * sizeof(cgtp::TileDesc), 256);
-    const size_t coefi_off = total;
-    total = align_up(total + h.coefi.size() * sizeof(int32_t), 256);
-    const size_t coefir_off = total;
-    total = align_up(total + h.coefir.size() * sizeof(int32_t), 256);
-    std::vector<char> host(total, 0);
-    if (!h.tdesc.empty())
-        std::memcpy(host.data() + tdesc_off, h.tdesc.data(), h.tdesc.size() * sizeof(cgtp::TileDesc));
-    if (!h.coefi.empty()) std::memcpy(host.data() + coefi_off, h.coefi.data(), h.coefi.size() * sizeof(int32_t));
-    if (!h.coefir.empty())
-        std::memcpy(host.data() + coefir_off, h.coefir.data(), h.coefir.size() * sizeof(int32_t));
-    for (int i = 0; i < kParts; ++i)
-        if (!parts[i]->empty()) std::memcpy(host.data() + offs[i], parts[i]->data(), parts[i]->size() * sizeof(T));
-    std::memcpy(host.data() + offs[kParts], blocks.data(), blocks.size() * sizeof(BlockDesc));
-    std::memcpy(host.data() + offs[kParts + 1], list.data(), list.size() * sizeof(int32_t));
-    hipError_t e = hipMalloc(&p->dmem, total);
-    if (e != hipSuccess) {
-        g_last_hip_error = (int)e;
-        p->dmem = nullptr;
-        return e == hipErrorOutOfMemory ? CGTP_ENOMEM : CGTP_EHIP;
-    }
-    e = hipMemcpy(p->dmem, host.data(), total, hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        g_last_hip_error = (int)e;
-        (void)hipFree(p->dmem);
-        p->dmem = nullptr;
-        return CGTP_EHIP;
-    }
-    p->dbytes = total;
-    char* base = (char*)p->dmem;
-    tb->pbar = (const T*)(base + offs[0]);
-    tb->wtab = (const T*)(base + offs[1]);
-    tb->tw = (const T*)(base + offs[2]);
-    tb->lcg = (const T*)(base + offs[3]);
-    tb->coef = (const T*)(base + offs[4]);
-    tb->coefi = (const int32_t*)(base + coefi_off);
-    tb->coefr = (const T*)(base + offs[5]);
-    tb->coefir = (const int32_t*)(base + coefir_off);
-    tb->wtab_len = (int32_t)h.wtab.size();
-    tb->blocks = (const BlockDesc*)(base + offs[kParts]);
-    tb->tdesc = (const cgtp::TileDesc*)(base + tdesc_off);
-    p->d_list = (const int32_t*)(base + offs[kParts + 1]);
-    p->d_bwd_list = p->d_list + p->bwd_list_off;
-    return CGTP_OK;
-}
-
-template <typename T>
-int upload_direct(cgtp_plan_s* p, cgtp::DirTables<T>* tb) {
-    cgtp::DirHost<T> h;
-    cgtp::dir_build<T>(p->L, h);
-    cgtp::DgHost d;   // gradients: fp32 (fp64 plans keep the sphere-grid kernel's)
-    if (sizeof(T) == 4) cgtp::dg_build(p->L, d);
+// Tables of a plan on their way to its device allocation.
+struct Image {
     struct Part {
         const void* src;
         size_t bytes, off;
     };
-    auto part = [](const auto& v) { return Part{v.data(), v.size() * sizeof(v[0]), 0}; };
-    Part parts[9] = {part(h.coef), part(h.items), part(h.stages), part(h.groups), part(d.coef),
-                     part(d.tasks), part(d.outs), part(d.parts), part(d.stages)};
+    std::vector<Part> parts;
     size_t total = 0;
-    for (auto& q : parts) {
-        q.off = total;
-        total = align_up(total + q.bytes, 256);
+    template <typename V> size_t add(const std::vector<V>& v) {
+        const size_t off = total;
+        parts.push_back({v.data(), v.size() * sizeof(V), off});
+        total = align_up(total + v.size() * sizeof(V), 256);
+        return off;
     }
-    hipError_t e = hipMalloc(&p->dmem_dir, total);
+};
+
+// Builds the direct contraction's tables where the plan has them and uploads
+// everything as one allocation.
+template <typename T>
+int upload(cgtp_plan_s* p, const std::vector<BlockDesc>& blocks, const HostTables<T>& h,
+           const std::vector<int32_t>& list, cgtp::Tables<T>* tb, cgtp::DirTables<T>* db) {
+    Image im;
+    const size_t pbar = im.add(h.pbar), wtab = im.add(h.wtab), tw = im.add(h.tw), lcg = im.add(h.lcg);
+    const size_t coef = im.add(h.coef), coefr = im.add(h.coefr), blk = im.add(blocks), lst = im.add(list);
+    const size_t tdesc = im.add(h.tdesc), coefi = im.add(h.coefi), coefir = im.add(h.coefir);
+    cgtp::DirHost<T> f;
+    cgtp::DgHost g;   // gradients: fp32 (fp64 plans keep the sphere-grid kernel's)
+    if (p->direct) cgtp::dir_build<T>(p->L, f);
+    if (p->direct && sizeof(T) == 4) cgtp::dg_build(p->L, g);
+    const size_t fcoef = im.add(f.coef), fitems = im.add(f.items), fstages = im.add(f.stages), fgroups = im.add(f.groups);
+    const size_t gcoef = im.add(g.coef), gtasks = im.add(g.tasks), gouts = im.add(g.outs), gparts = im.add(g.parts);
+    const size_t gstages = im.add(g.stages);
+    hipError_t e = hipMalloc(&p->dmem, im.total);
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
-        p->dmem_dir = nullptr;
+        p->dmem = nullptr;
         return e == hipErrorOutOfMemory ? CGTP_ENOMEM : CGTP_EHIP;
     }
-    char* base = (char*)p->dmem_dir;
-    auto copy = [&](size_t off, const void* src, size_t n) {
-        if (e == hipSuccess && n) e = hipMemcpy(base + off, src, n, hipMemcpyHostToDevice);
-    };
-    if (total <= ((size_t)1 << 20)) {   // small plans: one copy
-        std::vector<char> host(total, 0);
-        for (const auto& q : parts)
+    char* base = (char*)p->dmem;
+    if (im.total <= ((size_t)1 << 20)) {   // small plans: one copy
+        std::vector<char> host(im.total, 0);
+        for (const auto& q : im.parts)
             if (q.bytes) std::memcpy(host.data() + q.off, q.src, q.bytes);
-        copy(0, host.data(), total);
+        e = hipMemcpy(base, host.data(), im.total, hipMemcpyHostToDevice);
     } else {
-        for (const auto& q : parts) copy(q.off, q.src, q.bytes);
+        for (const auto& q : im.parts)
+            if (e == hipSuccess && q.bytes) e = hipMemcpy(base + q.off, q.src, q.bytes, hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
         return CGTP_EHIP;
     }
-    tb->coef = (const T*)(base + parts[0].off);
-    tb->items = (const cgtp::DirItem*)(base + parts[1].off);
-    tb->stages = (const cgtp::DirStage*)(base + parts[2].off);
-    tb->groups = (const cgtp::DirGroup*)(base + parts[3].off);
-    for (int i = 0; i < 2; ++i) tb->lists[i] = h.lists[i];
-    p->dg.coef = (const float*)(base + parts[4].off);
-    p->dg.tasks = (const cgtp::DgTask*)(base + parts[5].off);
-    p->dg.outs = (const cgtp::DgOut*)(base + parts[6].off);
-    p->dg.parts = (const cgtp::DgPart*)(base + parts[7].off);
-    p->dg.stages = (const cgtp::DgStage*)(base + parts[8].off);
-    for (int i = 0; i < 2; ++i) p->dg.lists[i] = d.lists[i];
+    p->dbytes = im.total;
+    tb->pbar = (const T*)(base + pbar);
+    tb->wtab = (const T*)(base + wtab);
+    tb->tw = (const T*)(base + tw);
+    tb->lcg = (const T*)(base + lcg);
+    tb->coef = (const T*)(base + coef);
+    tb->coefi = (const int32_t*)(base + coefi);
+    tb->coefr = (const T*)(base + coefr);
+    tb->coefir = (const int32_t*)(base + coefir);
+    tb->wtab_len = (int32_t)h.wtab.size();
+    tb->blocks = (const BlockDesc*)(base + blk);
+    tb->tdesc = (const cgtp::TileDesc*)(base + tdesc);
+    p->d_list = (const int32_t*)(base + lst);
+    p->d_bwd_list = p->d_list + p->bwd_list_off;
+    db->coef = (const T*)(base + fcoef);
+    db->items = (const cgtp::DirItem*)(base + fitems);
+    db->stages = (const cgtp::DirStage*)(base + fstages);
+    db->groups = (const cgtp::DirGroup*)(base + fgroups);
+    p->dg.coef = (const float*)(base + gcoef);
+    p->dg.tasks = (const cgtp::DgTask*)(base + gtasks);
+    p->dg.outs = (const cgtp::DgOut*)(base + gouts);
+    p->dg.parts = (const cgtp::DgPart*)(base + gparts);
+    p->dg.stages = (const cgtp::DgStage*)(base + gstages);
+    for (int i = 0; i < 2; ++i) {
+        db->lists[i] = f.lists[i];
+        p->dg.lists[i] = g.lists[i];
+    }
     return CGTP_OK;
 }
 
@@ -1065,12 +1032,11 @@ int cgtp_plan(int32_t L, const cgtp_grid* grid, cgtp_plan_t* plan_out) {
     if (g.dtype == CGTP_FP32) {
         HostTables<float> h;
         rc = build<float>(p, blocks, h, list);
-        if (rc == CGTP_OK) rc = p->direct ? upload_direct<float>(p, &p->df) : upload<float>(p, blocks, h, list, &p->tf);
+        if (rc == CGTP_OK) rc = upload<float>(p, blocks, h, list, &p->tf, &p->df);
     } else {
         HostTables<double> h;
         rc = build<double>(p, blocks, h, list);
-        if (rc == CGTP_OK) rc = upload<double>(p, blocks, h, list, &p->td);   // direct plans: for the gradients
-        if (rc == CGTP_OK && p->direct) rc = upload_direct<double>(p, &p->dd);
+        if (rc == CGTP_OK) rc = upload<double>(p, blocks, h, list, &p->td, &p->dd);
     }
     if (rc != CGTP_OK) {
         (void)cgtp_destroy(p);
@@ -1085,10 +1051,6 @@ int cgtp_destroy(cgtp_plan_t plan) {
     int rc = CGTP_OK;
     if (plan->dmem) {
         hipError_t e = hipFree(plan->dmem);
-        if (e != hipSuccess) { g_last_hip_error = (int)e; rc = CGTP_EHIP; }
-    }
-    if (plan->dmem_dir) {
-        hipError_t e = hipFree(plan->dmem_dir);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = CGTP_EHIP; }
     }
     delete plan;

@@ -19,6 +19,8 @@ int oracle_cgtp_backward(int L, int64_t N, const double* x1, const double* x2, c
                          double* gx2, int nthreads);
 }
 
+int stub_allocations(bool succeed);
+
 static int fails = 0;
 #define EXPECT(cond)                                                       \
     do {                                                                   \
@@ -50,6 +52,16 @@ int main() {
         EXPECT(cgtp_plan(33, nullptr, &p) == CGTP_EUNSUP);
         EXPECT(cgtp_plan(-1, nullptr, &p) == CGTP_EINVAL);
     }
+    // the upload: one allocation per plan, given back by cgtp_destroy (a leak ends the run)
+    for (const cgtp_grid& g : {cgtp_grid{0, 0, CGTP_FP32, 0}, cgtp_grid{0, 0, CGTP_FP64, 0}, cgtp_grid{0, 0, CGTP_FP32, 1},
+                               cgtp_grid{20, 0, CGTP_FP64, 0}})
+        for (int L : {0, 3, 8}) {
+            cgtp_plan_t p = nullptr;
+            (void)stub_allocations(true);
+            EXPECT(cgtp_plan(L, &g, &p) == CGTP_OK && p);
+            EXPECT(stub_allocations(false) == 1);
+            EXPECT(cgtp_destroy(p) == CGTP_OK);
+        }
     std::printf("cgtp plans done\n");
     // exported host maths
     for (int j1 = 0; j1 <= 12; ++j1)

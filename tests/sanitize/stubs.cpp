@@ -1,23 +1,44 @@
 // Sanitizer build of the plan sources: stand-ins for the HIP runtime calls the
 // plans make and for the kernel launchers (no GPU, no device code).  The device
-// is 0; every allocation fails, so a plan runs all of its host maths and table
-// building and then returns CGTP_ENOMEM; every launch reports an error.
+// is 0; allocations fail, so a plan runs all of its host maths and table
+// building and then returns CGTP_ENOMEM, until stub_allocations lets them
+// succeed with host memory; every launch reports an error.
 #include <hip/hip_runtime.h>
+
+#include <cstdlib>
+#include <cstring>
 
 #include "../../paper_2602_21466_amd/csrc/cgtp_internal.h"
 #include "../../paper_2602_21466_amd/csrc/istp_internal.h"
+
+static bool alloc_ok = false;
+static int nallocs = 0;
+// Lets allocations succeed or not; returns how many were asked for since the last call.
+int stub_allocations(bool succeed) {
+    const int n = nallocs;
+    alloc_ok = succeed;
+    nallocs = 0;
+    return n;
+}
 
 extern "C" {
 hipError_t hipGetDevice(int* d) {
     *d = 0;
     return hipSuccess;
 }
-hipError_t hipMalloc(void** p, size_t) {
-    *p = nullptr;
-    return hipErrorOutOfMemory;
+hipError_t hipMalloc(void** p, size_t n) {
+    ++nallocs;
+    *p = alloc_ok ? std::malloc(n) : nullptr;
+    return *p ? hipSuccess : hipErrorOutOfMemory;
 }
-hipError_t hipFree(void*) { return hipSuccess; }
-hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipErrorInvalidValue; }
+hipError_t hipFree(void* p) {
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) {
+    std::memcpy(dst, src, n);
+    return hipSuccess;
+}
 }
 
 namespace cgtp {
