@@ -215,12 +215,12 @@ void dir_build(int L, DirHost<T>& h) {
             }
         }
     // long: a stage's run, per pair, takes up to 40 KiB (fp32) of LDS for the pairs
-    // of a work-group, so that two work-groups share a CU; four degrees of the
-    // largest block always fit.  A group takes blocks together until one filling of
+    // of a work-group, so that two work-groups share a CU, and at least the largest
+    // block's four largest degrees, (2 L + 1)^2 - (2 L - 3)^2 outputs.  A group takes blocks together until one filling of
     // the input tiles serves about four stages' worth of outputs (two stages: 1147 us
     // instead of 1105 at L = 16, N = 8192; 164 instead of 155 in the real basis at
     // L = 11, N = 4001; one stage 1211 and 185)
-    const int max_len = std::max(40 * 1024 / (dir_pairs<T>() * 4) - 1, 8 * L - 8);
+    const int max_len = std::max(40 * 1024 / (dir_pairs<T>() * 4) - 1, 16 * L - 8);
     dir_list<T>(L, first, max_len, 4 * max_len, false, h, h.lists[0]);
     // short: single stages of 256 (fp64: 128) outputs where that many are more than
     // four degrees of a block (half as many: 12.0 instead of 9.4 us in the real basis

@@ -862,6 +862,11 @@ int upload(cgtp_plan_s* p, const std::vector<BlockDesc>& blocks, const HostTable
     cgtp::DgHost g;   // gradients: fp32 (fp64 plans keep the sphere-grid kernel's)
     if (p->direct) cgtp::dir_build<T>(p->L, f);
     if (p->direct && sizeof(T) == 4) cgtp::dg_build(p->L, g);
+    for (int i = 0; i < 2; ++i) {   // (fp64 lists outgrow a CU's LDS at L = 26)
+        if (f.lists[i].lds_bytes > cgtp::kLdsBudget) return CGTP_EUNSUP;
+        for (int n : g.lists[i].lds_bytes)
+            if (n > cgtp::kLdsBudget) return CGTP_EUNSUP;
+    }
     const size_t fcoef = im.add(f.coef), fitems = im.add(f.items), fstages = im.add(f.stages), fgroups = im.add(f.groups);
     const size_t gcoef = im.add(g.coef), gtasks = im.add(g.tasks), gouts = im.add(g.outs), gparts = im.add(g.parts);
     const size_t gstages = im.add(g.stages);

@@ -25,6 +25,7 @@ template <typename T>
 static double run(int L, const DirHost<T>& h, const DirList& list) {
     constexpr int HM = dir_orders<T>(), KC = dir_kc<T>(), RS = dir_row<T>();
     const int nin = (L + 1) * (L + 1), nout = nin * nin;
+    need(list.lds_bytes <= kLdsBudget, "more LDS than a CU has");
     std::vector<double> x[2], out(nout, NAN);
     for (auto& r : x) {
         r.resize(nin);
@@ -126,6 +127,7 @@ static double backward(int L, const DgHost& h, const DgList& list) {
         for (int i = 0; i < list.nstages[cls]; ++i, ++si) {
             const DgStage& st = h.stages[(size_t)si];
             const int G = dg_groups(cls), P = dg_pairs(G), RS = dg_row(G), HM = dg_orders(G), KC = dg_kc(G);
+            need(list.lds_bytes[cls] <= kLdsBudget, "more LDS than a CU has");
             need(4 * (st.acc0 + st.acc_len) <= list.lds_bytes[cls] && st.acc0 % 4 == 0 && st.acc_len % 4 == 0,
                  "stage larger than the LDS of the launch");
             need((st.l1b + 1) * (st.l1b + 1) - st.l1a * st.l1a + (st.l2b + 1) * (st.l2b + 1) - st.l2a * st.l2a <= kDgMaxInputs,

@@ -42,7 +42,10 @@ def test_coefficients_match_the_racah_formula(model):
 
 @pytest.mark.parametrize("dtype,L", [("fp32", 0), ("fp32", 1), ("fp32", 2), ("fp32", 4), ("fp32", 7), ("fp32", 11),
                                      ("fp32", 16), ("fp64", 0), ("fp64", 3), ("fp64", 8),
-                                     ("backward", 0), ("backward", 3), ("backward", 8), ("backward", 17)])
+                                     ("backward", 0), ("backward", 3), ("backward", 8), ("backward", 17),
+                                     # the largest degrees; gradients of blocks in several parts (from 21)
+                                     ("fp32", 24), ("fp32", 32), ("fp64", 14), ("fp64", 19), ("backward", 21),
+                                     ("backward", 24), ("backward", 32)])
 def test_work_lists_cover_every_output_once(model, dtype, L):
     assert model(dtype, L) < TOL.get(dtype, 1e-6)
 
@@ -67,7 +70,8 @@ def _rows(torch, n, cols, dtype, seed):
 @pytest.mark.gpu
 @pytest.mark.parametrize("L,N,dtype", [(0, 1, "fp32"), (1, 15, "fp32"), (2, 16, "fp32"), (3, 17, "fp32"), (5, 33, "fp32"),
                                        (8, 3, "fp32"), (13, 18, "fp32"), (20, 2, "fp32"), (0, 33, "fp64"),
-                                       (2, 31, "fp64"), (4, 32, "fp64"), (9, 5, "fp64")])
+                                       (2, 31, "fp64"), (4, 32, "fp64"), (9, 5, "fp64"),
+                                       (27, 3, "fp32"), (32, 2, "fp32"), (14, 33, "fp64"), (19, 3, "fp64")])
 def test_forward_and_real_match_oracle(L, N, dtype):
     import torch
     import oracle
@@ -85,7 +89,9 @@ def test_forward_and_real_match_oracle(L, N, dtype):
 
 # ragged tiles of 16 and 8 pairs; the three classes of blocks (largest degrees up to 6, 16 and above)
 @pytest.mark.gpu
-@pytest.mark.parametrize("L,N", [(0, 1), (1, 17), (3, 15), (6, 33), (11, 16), (13, 9), (16, 8), (18, 5)])
+@pytest.mark.parametrize("L,N", [(0, 1), (1, 17), (3, 15), (6, 33), (11, 16), (13, 9), (16, 8), (18, 5),
+                                 # blocks in several parts
+                                 (21, 9), (27, 3), (32, 2)])
 def test_gradients_match_oracle(L, N):
     import torch
     import oracle
