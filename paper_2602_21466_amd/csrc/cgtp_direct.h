@@ -237,15 +237,13 @@ int dir_launches(int64_t total, int64_t per, int threads, F&& launch) {
     return 0;
 }
 
-// Weak, so that the plan's host code also links without the device code (it
-// never calls them then: no table can be uploaded).
-__attribute__((weak)) int launch_direct_f32(const DirTables<float>& tb, const float* x1, const float* x2, float* out, int64_t N, int L,
+int launch_direct_f32(const DirTables<float>& tb, const float* x1, const float* x2, float* out, int64_t N, int L,
                       const ChanArgs<float>* ch, bool real_basis, void* stream);
-__attribute__((weak)) int launch_direct_f64(const DirTables<double>& tb, const double* x1, const double* x2, double* out, int64_t N, int L,
+int launch_direct_f64(const DirTables<double>& tb, const double* x1, const double* x2, double* out, int64_t N, int L,
                       const ChanArgs<double>* ch, bool real_basis, void* stream);
 
-__attribute__((weak)) int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2, const float* g,
-                                                 float* gx1, float* gx2, float* ws, int64_t N, int L, void* stream);
+int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2, const float* g, float* gx1, float* gx2,
+                           float* ws, int64_t N, int L, void* stream);
 // The sums of the blocks' contributions (cgtp_backward.hip).
 int launch_backward_sums(const float* ws, float* gx1, float* gx2, int64_t N, int L, void* stream);
 

@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "../../paper_2602_21466_amd/csrc/cgtp_direct.h"
 #include "../../paper_2602_21466_amd/csrc/cgtp_internal.h"
 #include "../../paper_2602_21466_amd/csrc/istp_internal.h"
 
@@ -58,6 +59,12 @@ int launch_backward_f32(const Tables<float>&, const BwdLaunch&, const float*, co
                         float*, float*, int64_t, int, void*) { return 1; }
 int launch_backward_f64(const Tables<double>&, const BwdLaunch&, const double*, const double*, const double*,
                         double*, double*, double*, int64_t, int, void*) { return 1; }
+int launch_direct_f32(const DirTables<float>&, const float*, const float*, float*, int64_t, int, const ChanArgs<float>*,
+                      bool, void*) { return 1; }
+int launch_direct_f64(const DirTables<double>&, const double*, const double*, double*, int64_t, int,
+                      const ChanArgs<double>*, bool, void*) { return 1; }
+int launch_direct_backward(const DgTables&, const float*, const float*, const float*, float*, float*, float*, int64_t,
+                           int, void*) { return 1; }
 }  // namespace cgtp
 
 namespace istp {

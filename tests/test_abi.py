@@ -5,6 +5,8 @@ import ctypes
 import glob
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -32,6 +34,15 @@ def test_library_exports_every_declared_function():
     missing = [n for n in sorted(declared) if not hasattr(so, n)]
     assert not missing, missing
     assert declared == set(lib.exported_symbols())
+
+
+def test_no_launcher_is_weak():
+    """A library built without one of its kernel files has to fail to load, not call a null pointer."""
+    if shutil.which("nm") is None:
+        pytest.skip("no nm")
+    names = subprocess.run(["nm", "-DC", lib._build.LIB], capture_output=True, text=True, check=True).stdout
+    kinds = {m.group(2): m.group(1) for m in re.finditer(r"^\s*[0-9a-f]* (\w) ((?:cgtp|istp)::launch_\w+)", names, re.M)}
+    assert "cgtp::launch_direct_f32" in kinds and set(kinds.values()) == {"T"}, kinds
 
 
 def test_istp_row_layouts_match_the_oracle():
