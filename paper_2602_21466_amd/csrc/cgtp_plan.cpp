@@ -920,6 +920,16 @@ int upload(cgtp_plan_s* p, const std::vector<BlockDesc>& blocks, const HostTable
     return CGTP_OK;
 }
 
+// A plan's tables, on the host and on the device.
+template <typename T>
+int tables(cgtp_plan_s* p, cgtp::Tables<T>* tb, cgtp::DirTables<T>* db) {
+    std::vector<BlockDesc> blocks;
+    std::vector<int32_t> list;
+    HostTables<T> h;
+    const int rc = build<T>(p, blocks, h, list);
+    return rc == CGTP_OK ? upload<T>(p, blocks, h, list, tb, db) : rc;
+}
+
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
     const char *pa = (const char*)a, *pb = (const char*)b;
     return pa < pb + nb && pb < pa + na;
@@ -1032,16 +1042,10 @@ int cgtp_plan(int32_t L, const cgtp_grid* grid, cgtp_plan_t* plan_out) {
         delete p;
         return CGTP_EHIP;
     }
-    std::vector<BlockDesc> blocks;
-    std::vector<int32_t> list;
-    if (g.dtype == CGTP_FP32) {
-        HostTables<float> h;
-        rc = build<float>(p, blocks, h, list);
-        if (rc == CGTP_OK) rc = upload<float>(p, blocks, h, list, &p->tf, &p->df);
-    } else {
-        HostTables<double> h;
-        rc = build<double>(p, blocks, h, list);
-        if (rc == CGTP_OK) rc = upload<double>(p, blocks, h, list, &p->td, &p->dd);
+    try {
+        rc = g.dtype == CGTP_FP32 ? tables<float>(p, &p->tf, &p->df) : tables<double>(p, &p->td, &p->dd);
+    } catch (const std::bad_alloc&) {   // (100 MB of tables at L = 32)
+        rc = CGTP_ENOMEM;
     }
     if (rc != CGTP_OK) {
         (void)cgtp_destroy(p);

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <new>
 #include <vector>
 
 #include "../../include/cgtp.h"
@@ -20,6 +21,19 @@ int oracle_cgtp_backward(int L, int64_t N, const double* x1, const double* x2, c
 }
 
 int stub_allocations(bool succeed);
+
+// operator new fails once `left` more allocations were made (< 0: never)
+static long left = -1;
+void* operator new(std::size_t n) {
+    if (left >= 0 && left-- == 0) throw std::bad_alloc();
+    if (void* p = std::malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void* operator new(std::size_t n, const std::nothrow_t&) noexcept {
+    return left >= 0 && left-- == 0 ? nullptr : std::malloc(n ? n : 1);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 
 static int fails = 0;
 #define EXPECT(cond)                                                       \
@@ -62,6 +76,21 @@ int main() {
             EXPECT(stub_allocations(false) == 1);
             EXPECT(cgtp_destroy(p) == CGTP_OK);
         }
+    // host memory runs out at some point of the building: a status, no exception, nothing kept
+    for (const cgtp_grid& g : {cgtp_grid{0, 0, CGTP_FP32, 0}, cgtp_grid{0, 0, CGTP_FP64, 0}, cgtp_grid{0, 0, CGTP_FP32, 1}}) {
+        int rc = CGTP_ENOMEM, tries = 0;
+        (void)stub_allocations(true);
+        for (long n = 0; rc == CGTP_ENOMEM; n += 7, ++tries) {
+            cgtp_plan_t p = nullptr;
+            left = n;
+            rc = cgtp_plan(3, &g, &p);
+            left = -1;
+            EXPECT((rc == CGTP_OK) == (p != nullptr));
+            EXPECT(cgtp_destroy(p) == CGTP_OK);
+        }
+        EXPECT(rc == CGTP_OK && tries > 20);
+        (void)stub_allocations(false);
+    }
     std::printf("cgtp plans done\n");
     // exported host maths
     for (int j1 = 0; j1 <= 12; ++j1)
