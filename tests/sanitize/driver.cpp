@@ -1,6 +1,7 @@
 // Drives the host-side code of the library and the oracle under ASan/UBSan:
-// every plan's host maths and table building (cgtp_plan and istp_plan up to
-// L = 32, both dtypes, both covers, forced grids), the exported host maths,
+// every plan's host maths and table building (cgtp_plan up to L = 32: the direct
+// contraction's lists, and the sphere-grid tables of both covers, per block and
+// on a forced grid, both dtypes; istp_plan), its upload, the exported host maths,
 // istp_plan_describe, argument validation, and the oracle's products and
 // gradients.  Prints one line per section; any sanitizer report aborts it.
 #include <cmath>
@@ -47,16 +48,18 @@ static int fails = 0;
 int main() {
     // cgtp plans: host maths and tables, then the allocation stand-in fails
     for (int L : {0, 1, 2, 3, 5, 8, 16, 32})
-        for (int cover = 0; cover < 2; ++cover) {
-            cgtp_grid g{0, 0, CGTP_FP32, cover};
+        for (int cover = 0; cover < 2; ++cover)
+            for (int n_theta : {0, 2 * L + 2}) {   // (cover 0 without a grid: the direct contraction)
+                cgtp_grid g{n_theta, 0, CGTP_FP32, cover};
+                cgtp_plan_t p = nullptr;
+                EXPECT(cgtp_plan(L, &g, &p) == CGTP_ENOMEM && p == nullptr);
+            }
+    for (int L : {0, 4, 12, 19})
+        for (int n_theta : {0, 2 * L + 2}) {
+            cgtp_grid g{n_theta, 0, CGTP_FP64, 0};
             cgtp_plan_t p = nullptr;
-            EXPECT(cgtp_plan(L, &g, &p) == CGTP_ENOMEM && p == nullptr);
+            EXPECT(cgtp_plan(L, &g, &p) == CGTP_ENOMEM);
         }
-    for (int L : {0, 4, 12, 19}) {
-        cgtp_grid g{0, 0, CGTP_FP64, 0};
-        cgtp_plan_t p = nullptr;
-        EXPECT(cgtp_plan(L, &g, &p) == CGTP_ENOMEM);
-    }
     {
         cgtp_grid g{12, 27, CGTP_FP32, 0};   // one global grid for L = 5
         cgtp_plan_t p = nullptr;

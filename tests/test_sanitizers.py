@@ -2,9 +2,10 @@
 
 The plan sources (cgtp_plan.cpp, istp_plan.cpp) are built host-only with g++
 against a stand-in for the HIP runtime (tests/sanitize/: four runtime calls
-and the kernel launchers stubbed, allocations failing), together with the
+and the kernel launchers stubbed, allocations failing or from host memory), together with the
 oracle (oracle/cgtp_oracle.c), and driven by tests/sanitize/driver.cpp: every
-plan's host maths and table building up to L = 32, the exported host maths,
+plan's host maths, table building up to L = 32 and upload, plans for which
+host memory runs out, the exported host maths,
 istp_plan_describe, argument validation and the oracle's products and
 gradients.  Any sanitizer report (out-of-bounds access, leak, signed
 overflow, invalid shift, ...) ends the run with a non-zero status.
