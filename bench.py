@@ -46,35 +46,35 @@ MEASURED_TRAFFIC = {
     "07bd4ac232eb2a7d": {
         "cgtp_L16_N8192_fp32:backward": {"fetch_kib": 2046800.0, "fetch_scale": 1.999956, "write_kib": 332900.0, "write_scale": 1.000000},
     },
-    "c7165dffef5eff6e": {
+    "45be1166ae5549bd": {
         "vstp_L32_N16384_fp32": {"fetch_kib": 217106.9, "fetch_scale": 1.999956, "write_kib": 986776.2, "write_scale": 1.000000},
         "gtp_L32_N65536_fp32": {"fetch_kib": 286868.4, "fetch_scale": 1.999956, "write_kib": 1327525.3, "write_scale": 1.000000},
         "vstp_L16_N65536_fp32": {"fetch_kib": 227504.5, "fetch_scale": 1.999956, "write_kib": 1011543.4, "write_scale": 1.000000},
         "vstp_L16_N65536_fp32:backward": {"fetch_kib": 1068316.0, "fetch_scale": 1.999956, "write_kib": 522281.5, "write_scale": 1.000000},
         "tstp_L16_N16384_fp32": {"fetch_kib": 97086.0, "fetch_scale": 1.999956, "write_kib": 428170.1, "write_scale": 1.000000},
     },
-    "8f1e51cd32a343ae": {
+    "5eac802a6bc2ea23": {
         "gtp_real_L16_N65536_fp32": {"fetch_kib": 76038.7, "fetch_scale": 1.999956, "write_kib": 347086.7, "write_scale": 1.000000},
         "gtp_real_L16_N65536_fp32:backward": {"fetch_kib": 355974.0, "fetch_scale": 1.999956, "write_kib": 176640.0, "write_scale": 1.000000},
         "vstp_real_L16_N65536_fp32": {"fetch_kib": 228015.0, "fetch_scale": 1.999956, "write_kib": 1004179.2, "write_scale": 1.000000},
     },
-    "636ee2db894d691d": {
+    "97ecc201d17d7597": {
         "vstp_L16_N4096_C16_fp32_x2shared_weighted": {"fetch_kib": 170283.2, "fetch_scale": 1.999956, "write_kib": 962724.6, "write_scale": 1.000000},
     },
 }
 
 
+_CGTP_PLAN = ("cgtp_plan.cpp", "cgtp_internal.h", "cgtp_direct_plan.h", "cgtp_direct.h", "device_common.h")
+_ISTP_PLAN = ("istp_plan.cpp", "istp_internal.h", "cgtp_internal.h", "device_common.h")
 DIGEST_SOURCES = {
-    "cgtp": ("cgtp_direct.hip", "cgtp_direct.h", "cgtp_direct_plan.h", "device_common.h"),
-    "cgtp_backward": ("cgtp_direct_backward.hip", "cgtp_backward.hip", "cgtp_direct.h", "cgtp_direct_plan.h",
-                      "device_common.h"),
-    "cgtp_real": ("cgtp_direct.hip", "cgtp_direct.h", "cgtp_direct_plan.h", "device_common.h"),
-    "istp": ("istp_kernels.hip", "istp_kernels_tensor.hip", "istp_plan.cpp", "istp_internal.h", "device_common.h"),
-    "channels": ("cgtp_direct.hip", "cgtp_direct.h", "cgtp_direct_plan.h", "device_common.h"),
-    "istp_real": ("istp_kernels.hip", "istp_kernels_tensor.hip", "istp_kernels_real.hip", "istp_real.hip",
-                  "istp_plan.cpp", "istp_internal.h", "device_common.h"),
-    "istp_channels": ("istp_kernels.hip", "istp_kernels_channels.hip", "istp_kernels_channels_tensor.hip",
-                      "istp_plan.cpp", "istp_internal.h", "device_common.h"),
+    "cgtp": ("cgtp_direct.hip",) + _CGTP_PLAN,
+    "cgtp_backward": ("cgtp_direct_backward.hip", "cgtp_backward.hip") + _CGTP_PLAN,
+    "cgtp_real": ("cgtp_direct.hip",) + _CGTP_PLAN,
+    "channels": ("cgtp_direct.hip",) + _CGTP_PLAN,
+    "istp": ("istp_kernels.hip", "istp_kernels_tensor.hip") + _ISTP_PLAN,
+    "istp_real": ("istp_kernels.hip", "istp_kernels_tensor.hip", "istp_kernels_real.hip", "istp_real.hip") + _ISTP_PLAN,
+    "istp_channels": ("istp_kernels.hip", "istp_kernels_channels.hip",
+                      "istp_kernels_channels_tensor.hip") + _ISTP_PLAN,
 }
 
 

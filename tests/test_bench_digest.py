@@ -1,5 +1,8 @@
 """bench.py's kernel digest: it keys the recorded HBM counters to the code they
 were taken on, so it must ignore comments and layout and see every code change."""
+import os
+import re
+
 import bench
 
 
@@ -22,3 +25,14 @@ def test_every_kind_hashes():
     for kind in bench.DIGEST_SOURCES:
         d = bench.kernel_digest(kind)
         assert len(d) == 16 and int(d, 16) >= 0
+
+
+def test_digest_covers_plan_and_headers():
+    """Every local file that a listed source includes is listed, and so is the plan that picks and launches it."""
+    csrc = os.path.join(bench.ROOT, "paper_2602_21466_amd", "csrc")
+    for kind, names in bench.DIGEST_SOURCES.items():
+        assert ("istp_plan.cpp" if kind.startswith("istp") else "cgtp_plan.cpp") in names, kind
+        for name in names:
+            with open(os.path.join(csrc, name), encoding="utf-8") as f:
+                included = re.findall(r'#include "([^"/]+)"', f.read())
+            assert set(included) <= set(names), (kind, name, included)
