@@ -183,50 +183,31 @@ void dir_list(int L, const DirFirst& first, int max_len, int group_len, bool spl
     for (const auto& c : groups) h.groups.push_back(c.g);
 }
 
-// The coefficient table and the work lists of degree L.
+// Coefficients of block (la, lb), la <= lb, for the forward; first chunk of (row
+// group, orders m0..).
 template <typename T>
-void dir_build(int L, DirHost<T>& h) {
+void dir_coefs(int la, int lb, const std::vector<std::vector<double>>& cg, DirHost<T>& h,
+               std::vector<std::vector<int>>& f) {
     constexpr int KC = dir_kc<T>(), HM = dir_orders<T>();
-    // coefficients of the blocks la <= lb: first chunk of (row group, orders m0..)
-    DirFirst first;
-    std::vector<std::vector<double>> cg;
-    for (int la = 0; la <= L; ++la)
-        for (int lb = la; lb <= L; ++lb) {
-            dir_cg_block(la, lb, cg);
-            auto& f = first[{la, lb}];
-            f.resize((size_t)(2 * la + 1 + kDirRows - 1) / kDirRows);
-            for (int rg = 0; rg < (int)f.size(); ++rg) {
-                const int lt = la + lb - kDirRows * rg;
-                for (int m0 = 0; m0 <= lt; m0 += HM) {
-                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
-                    const int nch = (nk + KC - 1) / KC;
-                    const size_t at = h.coef.size();
-                    f[(size_t)rg].push_back((int)(at / kDirChunk));
-                    h.coef.resize(at + (size_t)nch * kDirChunk, (T)0);
-                    for (int o = 0; o < HM && m0 + o <= lt; ++o) {
-                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
-                        const auto& a = cg[(size_t)(m0 + o)];
-                        for (int r = 0; r < kDirRows && kDirRows * rg + r < n; ++r)
-                            for (int k = 0; k < n; ++k)
-                                h.coef[at + (size_t)(k / KC) * kDirChunk + dir_coef_index<T>(k % KC, o, r)] =
-                                    (T)a[(size_t)(kDirRows * rg + r) * n + k];
-                    }
-                }
+    f.resize((size_t)(2 * la + 1 + kDirRows - 1) / kDirRows);
+    for (int rg = 0; rg < (int)f.size(); ++rg) {
+        const int lt = la + lb - kDirRows * rg;
+        for (int m0 = 0; m0 <= lt; m0 += HM) {
+            const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
+            const int nch = (nk + KC - 1) / KC;
+            const size_t at = h.coef.size();
+            f[(size_t)rg].push_back((int)(at / kDirChunk));
+            h.coef.resize(at + (size_t)nch * kDirChunk, (T)0);
+            for (int o = 0; o < HM && m0 + o <= lt; ++o) {
+                const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
+                const auto& a = cg[(size_t)(m0 + o)];
+                for (int r = 0; r < kDirRows && kDirRows * rg + r < n; ++r)
+                    for (int k = 0; k < n; ++k)
+                        h.coef[at + (size_t)(k / KC) * kDirChunk + dir_coef_index<T>(k % KC, o, r)] =
+                            (T)a[(size_t)(kDirRows * rg + r) * n + k];
             }
         }
-    // long: a stage's run, per pair, takes up to 40 KiB (fp32) of LDS for the pairs
-    // of a work-group, so that two work-groups share a CU, and at least the largest
-    // block's four largest degrees, (2 L + 1)^2 - (2 L - 3)^2 outputs.  A group takes blocks together until one filling of
-    // the input tiles serves about four stages' worth of outputs (two stages: 1147 us
-    // instead of 1105 at L = 16, N = 8192; 164 instead of 155 in the real basis at
-    // L = 11, N = 4001; one stage 1211 and 185)
-    const int max_len = std::max(40 * 1024 / (dir_pairs<T>() * 4) - 1, 16 * L - 8);
-    dir_list<T>(L, first, max_len, 4 * max_len, false, h, h.lists[0]);
-    // short: single stages of 256 (fp64: 128) outputs where that many are more than
-    // four degrees of a block (half as many: 12.0 instead of 9.4 us in the real basis
-    // at L = 16, N = 16; twice as many: 11.0 instead of 7.8 in fp64 at L = 4, N = 100)
-    const int short_len = 4096 / dir_pairs<T>();
-    dir_list<T>(L, first, short_len, short_len, true, h, h.lists[1]);
+    }
 }
 
 struct DgHost {
@@ -384,39 +365,62 @@ inline void dg_list(int L, const DgFirst& first, int max_len, DgHost& h, DgList&
     }
 }
 
-// The gradient kernel's table and work lists of degree L.
-inline void dg_build(int L, DgHost& h) {
+// The same for the gradients; first chunk of each task.
+inline void dg_coefs(int la, int lb, const std::vector<std::vector<double>>& cg, DgHost& h, std::vector<int>& first) {
+    const int G = dg_groups(dg_class(la, lb)), HM = dg_orders(G), KC = dg_kc(G);
+    const int nrg = (2 * la + 1 + 3) / 4;
+    for (int rg0 = 0; rg0 < nrg; rg0 += kDgRows) {
+        const int rgs = std::min(kDgRows, nrg - rg0);
+        first.push_back((int)(h.coef.size() / kDirChunk));
+        for (int m0 = 0; m0 <= la + lb; m0 += HM) {
+            const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
+            if (nk <= 4 * rg0) break;
+            const int nch = (nk + KC - 1) / KC;
+            const size_t at = h.coef.size();
+            h.coef.resize(at + (size_t)nch * rgs * kDirChunk, 0.0f);
+            for (int o = 0; o < HM && m0 + o <= la + lb; ++o) {
+                const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
+                const auto& a = cg[(size_t)(m0 + o)];
+                for (int s = 0; s < n; ++s)
+                    for (int r = 0; r < 4 * rgs && 4 * rg0 + r < n; ++r)
+                        h.coef[at + ((size_t)(s / KC) * rgs + r / 4) * kDirChunk + dg_coef_index(G, s % KC, o, r % 4)] =
+                            (float)a[(size_t)s * n + 4 * rg0 + r];
+            }
+        }
+    }
+}
+
+// The coefficient table and the work lists of degree L, and with `g` the
+// gradient kernel's.
+template <typename T>
+void dir_build(int L, DirHost<T>& h, DgHost* g = nullptr) {
+    DirFirst first;
+    DgFirst gfirst;
     std::vector<std::vector<double>> cg;
-    DgFirst first;
     for (int la = 0; la <= L; ++la)
         for (int lb = la; lb <= L; ++lb) {
             dir_cg_block(la, lb, cg);
-            const int G = dg_groups(dg_class(la, lb)), HM = dg_orders(G), KC = dg_kc(G);
-            const int nrg = (2 * la + 1 + 3) / 4;
-            for (int rg0 = 0; rg0 < nrg; rg0 += kDgRows) {
-                const int rgs = std::min(kDgRows, nrg - rg0);
-                first[{la, lb}].push_back((int)(h.coef.size() / kDirChunk));
-                for (int m0 = 0; m0 <= la + lb; m0 += HM) {
-                    const int nk = std::min(2 * la + 1, la + lb - m0 + 1);
-                    if (nk <= 4 * rg0) break;
-                    const int nch = (nk + KC - 1) / KC;
-                    const size_t at = h.coef.size();
-                    h.coef.resize(at + (size_t)nch * rgs * kDirChunk, 0.0f);
-                    for (int o = 0; o < HM && m0 + o <= la + lb; ++o) {
-                        const int n = std::min(2 * la + 1, la + lb - m0 - o + 1);
-                        const auto& a = cg[(size_t)(m0 + o)];
-                        for (int s = 0; s < n; ++s)
-                            for (int r = 0; r < 4 * rgs && 4 * rg0 + r < n; ++r)
-                                h.coef[at + ((size_t)(s / KC) * rgs + r / 4) * kDirChunk +
-                                       dg_coef_index(G, s % KC, o, r % 4)] = (float)a[(size_t)s * n + 4 * rg0 + r];
-                    }
-                }
-            }
+            dir_coefs<T>(la, lb, cg, h, first[{la, lb}]);
+            if (g) dg_coefs(la, lb, cg, *g, gfirst[{la, lb}]);
         }
-    h.coef.resize(h.coef.size() + (size_t)kDgRows * kDirChunk, 0.0f);   // read ahead of the last chunk
-    dg_list(L, first, INT32_MAX, h, h.lists[0]);
+    // long: a stage's run, per pair, takes up to 40 KiB (fp32) of LDS for the pairs
+    // of a work-group, so that two work-groups share a CU, and at least the largest
+    // block's four largest degrees, (2 L + 1)^2 - (2 L - 3)^2 outputs.  A group takes blocks together until one filling of
+    // the input tiles serves about four stages' worth of outputs (two stages: 1147 us
+    // instead of 1105 at L = 16, N = 8192; 164 instead of 155 in the real basis at
+    // L = 11, N = 4001; one stage 1211 and 185)
+    const int max_len = std::max(40 * 1024 / (dir_pairs<T>() * 4) - 1, 16 * L - 8);
+    dir_list<T>(L, first, max_len, 4 * max_len, false, h, h.lists[0]);
+    // short: single stages of 256 (fp64: 128) outputs where that many are more than
+    // four degrees of a block (half as many: 12.0 instead of 9.4 us in the real basis
+    // at L = 16, N = 16; twice as many: 11.0 instead of 7.8 in fp64 at L = 4, N = 100)
+    const int short_len = 4096 / dir_pairs<T>();
+    dir_list<T>(L, first, short_len, short_len, true, h, h.lists[1]);
+    if (!g) return;
+    g->coef.resize(g->coef.size() + (size_t)kDgRows * kDirChunk, 0.0f);   // read ahead of the last chunk
+    dg_list(L, gfirst, INT32_MAX, *g, g->lists[0]);
     // (128 outputs: 16.5 instead of 14.3 us at L = 3, N = 100)
-    dg_list(L, first, 64, h, h.lists[1]);
+    dg_list(L, gfirst, 64, *g, g->lists[1]);
 }
 
 }  // namespace cgtp

@@ -228,8 +228,9 @@ static double backward(int L, const DgHost& h, const DgList& list) {
 }
 
 static double gradients(int L) {
+    DirHost<float> f;
     DgHost h;
-    dg_build(L, h);
+    dir_build<float>(L, f, &h);
     srand48(1);
     const double a = backward(L, h, h.lists[0]);
     srand48(1);
