@@ -17,9 +17,10 @@
  * for the alternate cover), transformed back, and each path is divided by the
  * factor the generalized Gaunt formula (Theorem 4.2) fixes.  Corollary 5.3 is
  * what makes one such product per block enough.  A plan that leaves both open
- * (n_theta = n_phi = 0, default cover) contracts the coefficients directly on
- * the matrix cores, order by order: up to L = 32 that is the faster route, a
- * fifth of the arithmetic and bound by writing the outputs.
+ * (n_theta = n_phi = 0, default cover) contracts the coefficients directly,
+ * order by order (fp32 on the matrix cores): up to L = 32 that is the faster
+ * route, a fifth of the arithmetic, and bound by the rate at which a CU issues
+ * instructions.
  *
  * Conventions: complex spherical basis with Condon-Shortley phase
  * (quantum-mechanics conventions, footnote of Section 3.3); coefficients are
@@ -71,7 +72,9 @@ enum cgtp_cover {
 #define CGTP_MAX_L 32
 
 /*
- * Grid choice.  A zero field takes the default.
+ * Grid choice.  A zero field takes the default.  With n_theta, n_phi and cover
+ * all zero the plan contracts directly and uses no grid; its facts (queries) are
+ * those of the default grids.
  *   n_theta: 0 -> per-block minimal exact Gauss-Legendre grid (2*floor((l1+l2)/2)+2
  *            nodes); else one grid for all blocks with this many nodes, which
  *            must be even and >= 2L+2 (else CGTP_EGRID for < 2L+1, CGTP_EUNSUP
@@ -92,13 +95,16 @@ typedef struct {
 typedef struct cgtp_plan_s *cgtp_plan_t;
 
 /*
- * Builds a plan for degree L on the current HIP device: quadrature nodes,
+ * Builds a plan for degree L on the current HIP device and uploads its tables
+ * to device memory the plan owns: for the sphere-grid route quadrature nodes,
  * normalised associated Legendre tables, Clebsch-Gordan tables for the lifts
- * and the recombination, and 1/K for every path (Theorem 4.2), uploaded to
- * device memory the plan owns.  grid == NULL takes every default.
+ * and the recombination, and 1/K for every path (Theorem 4.2); for the direct
+ * contraction the Clebsch-Gordan matrices of every block and the lists of the
+ * work (in fp64 also the sphere-grid tables that the gradients read).
+ * grid == NULL takes every default.
  * Returns CGTP_EINVAL (L < 0, plan_out NULL), CGTP_EUNSUP (L > CGTP_MAX_L,
- * or a block whose projection accumulators do not fit one work-group: fp64
- * plans support L <= 19), CGTP_EDTYPE, CGTP_EGRID, CGTP_ENOMEM or CGTP_EHIP;
+ * or a block whose projection accumulators do not fit one work-group, on
+ * either route: fp64 plans support L <= 19), CGTP_EDTYPE, CGTP_EGRID, CGTP_ENOMEM or CGTP_EHIP;
  * *plan_out is set only on success.  Not timed work: call once per (L, grid).
  */
 int cgtp_plan(int32_t L, const cgtp_grid *grid, cgtp_plan_t *plan_out);
@@ -188,8 +194,8 @@ int cgtp_backward(cgtp_plan_t plan, const void *x1, const void *x2, const void *
 int64_t cgtp_backward_workspace_bytes(cgtp_plan_t plan, int64_t N);
 
 /*
- * Model counts per pair of cgtp_backward (both gradients): the forward's
- * algorithmic flops (cgtp_plan_query) plus the adjoint's extra work, i.e. the
+ * Model counts per pair of cgtp_backward (both gradients) by the sphere-grid
+ * method, whichever route the plan takes: the forward's algorithmic flops (cgtp_plan_query) plus the adjoint's extra work, i.e. the
  * products' adjoint forms both factors' gradients (the products term twice)
  * and the transposed synthesis costs what the lift does; compulsory bytes:
  * x1, x2, grad_x1, grad_x2 and grad_out, each once.  Either pointer may be
@@ -208,10 +214,12 @@ int cgtp_backward_query(cgtp_plan_t plan, double *flops_per_pair, double *bytes_
  * in the real basis, odd l1 + l2 + l3 paths (anti-Hermitian) after a factor i.
  * So the even paths are the real Gaunt integrals over K (Theorem 4.2 read in the
  * real basis) and path (1, 1, 1) is the cross product over sqrt(2) in the real
- * basis' (y, z, x) order.  One launch of the block kernel's real-basis
- * variant: the inputs' Hermitian coefficients make every lifted signal real
- * (or i times real, or a conjugate pair), so a cross block still needs two
- * transforms per input; the end phase forms the real-basis outputs.
+ * basis' (y, z, x) order.  Direct contraction: the forward kernel with the
+ * real and imaginary part of each path's orders >= 0 where the complex basis
+ * has the two signs.  Sphere grid: the block kernel's real-basis variant; the
+ * inputs' Hermitian coefficients make every lifted signal real (or i times
+ * real, or a conjugate pair), so a cross block still needs two transforms per
+ * input, and the end phase forms the real-basis outputs.
  *   workspace, workspace_bytes: unused (kept for callers of an earlier version
  *   that needed one); workspace may be NULL, workspace_bytes must be >= 0.
  * Rules otherwise as cgtp_forward.  Allocates nothing; asynchronous on
@@ -242,7 +250,9 @@ int64_t cgtp_num_outputs(int32_t L);
 int64_t cgtp_path_offset(int32_t L, int32_t l1, int32_t l2, int32_t l3);
 
 /*
- * Plan facts: the largest grid used (n_theta, n_phi), the smallest |K| over
+ * Plan facts.  Grid, K and flops are those of the sphere-grid method, also for
+ * a plan that contracts directly (which does about a fifth of these flops): the
+ * largest grid (n_theta, n_phi) that the method uses, the smallest |K| over
  * the recovered paths, the algorithmic flops per pair of the method (every
  * block on its minimal exact grid: lifts, longitude transforms at
  * 2.5 n log2 n flops per Hermitian transform of n points, pointwise products,

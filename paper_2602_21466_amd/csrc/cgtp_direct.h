@@ -105,8 +105,6 @@ struct DirTables {
 // L = 13, 100 29 / 17 (1540); L = 8, 1000 23.3 / 24.4 (2205); L = 11, 300 20 / 25 (2223).)
 constexpr int64_t kDirShortMax = 6 * 256;
 
-// fp32 coefficients of a chunk: element (lane, mi) at 4 lane + mi with
-// lane = ((group of orders) kc + k) 4 + row; fp64: (k, mi, row) at 16 k + 4 mi + row.
 // Elements from one pair's run in LDS to the next: room for its offset from a
 // 16-byte boundary, and an odd number of 16-byte units, so that the pairs of a
 // wave start on different banks.
@@ -115,6 +113,8 @@ template <typename T> __host__ __device__ inline int dir_run(int len) {
     return ((len + v - 1 + v - 1) / v | 1) * v;
 }
 
+// fp32 coefficients of a chunk: element (lane, mi) at 4 lane + mi with
+// lane = ((group of orders) kc + k) 4 + row; fp64: (k, mi, row) at 16 k + 4 mi + row.
 template <typename T> __host__ __device__ inline int dir_coef_index(int k, int order, int row);
 template <> __host__ __device__ inline int dir_coef_index<float>(int k, int order, int row) {
     return (((order >> 2) * dir_kc<float>() + k) * 4 + row) * 4 + (order & 3);

@@ -9,13 +9,15 @@
 // in LDS in output order, and then write them as whole runs.
 //
 // Bound by instruction issue: the vector units issue in 59 % of the SIMD cycles
-// at L = 16 (55 % at L = 32), the matrix cores work in 19 % (25 %).  A loop of
-// this mix alone (4 products and 2 LDS reads per 4 MFMAs) reaches 77 TFLOP/s at
-// four waves per SIMD, 68 at two; the bare instruction 125.  Two work-groups per
-// CU, so that one computes while the other stores.  Measured (us, sphere-grid
-// kernels before / now): L = 16, 8192 pairs 13467 / 1057; L = 32, 1024 pairs
-// 22259 / 2182 (2.2 TB/s of outputs); real basis L = 11, 4001 pairs 2412 / 158;
-// 16 weighted channels, L = 16, 8192 rows 14582 / 1212.
+// at L = 16 (54 % at L = 32), the matrix cores work in 19 % (25 %).  Most of it
+// is not the k loop: per item and wave 286 (352) vector instructions besides the
+// MFMAs, of which 54 (105) are the products and the other 230 to 250 the item's
+// fixed cost: 16 accumulators cleared, 16 results each compared, masked, signed,
+// addressed and stored.  Two work-groups per CU, so that one computes while the
+// other stores.  Measured (us, sphere-grid kernels before / now): L = 16, 8192
+// pairs 13467 / 1053; L = 32, 1024 pairs 22259 / 2175 (2.2 TB/s of outputs); real
+// basis L = 11, 4001 pairs 2412 / 157; 16 weighted channels, L = 16, 8192 rows
+// 14582 / 1171; one pair, fp64, L = 16 36 / 24.
 // The 16x16x4 instruction takes 1948 us at L = 32, but 258 against 117 at L = 4
 // (100000 pairs) and 191 against 162 in the real basis at L = 11.
 

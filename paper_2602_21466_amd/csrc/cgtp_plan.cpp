@@ -1,8 +1,8 @@
 // Host side of the CGTP library: the math the plan is built from, the plan
 // itself (tables uploaded to device memory) and the C ABI entry points.
 //
-// Everything here runs once per plan and is not timed.  The device work is in
-// cgtp_kernels.hip.
+// Everything here runs once per plan and is not timed, but for the entry points'
+// checks and launches.  The device work is in the .hip files.
 
 #include <hip/hip_runtime.h>
 
@@ -363,11 +363,14 @@ struct cgtp_plan_s {
     double bwd_flops_per_pair = 0;
     double cross_cg = 0, dot_cg = 0;
     // Plans without a grid or cover of the caller's choice run the direct
-    // contraction: the same outputs, and the faster route at every size timed
-    // (us, sphere-grid kernels against direct: fp64 L = 2, 64 pairs 15.6 / 9.8;
-    // fp32 L = 4, 100000 pairs 3628 / 117; L = 16, 8192 13467 / 1057; L = 32, 1024
-    // 22259 / 2182; gradients L = 16 33102 / 2407).  A grid or cover that the
-    // caller chose is what they get.  fp64 gradients stay on the sphere-grid
+    // contraction: the same outputs, and the faster route for forward, real basis,
+    // channels and fp32 gradients at every degree and number of pairs timed, 1 to
+    // 200000 pairs, fp32 L = 0 to 32, fp64 0 to 19 (us, sphere-grid kernels against
+    // direct, the nearest and some others: fp64 L = 0, 1 pair 9.4 / 8.1; L = 16, 1
+    // 36.1 / 24.0; L = 19, 1 57.8 / 41.9; L = 8, 20456 11311 / 751; fp32 L = 4, 100000
+    // 3628 / 116; L = 32, 1024 22259 / 2175; gradients L = 2 to 4, 16 pairs, a call of
+    // launches on either route, 15.5 / 15.6; L = 16, 8192 33102 / 2140).  A grid or cover
+    // that the caller chose is what they get.  fp64 gradients stay on the sphere-grid
     // kernels: the direct ones are written for the fp32 matrix instruction only.
     bool direct = false;
     cgtp::DirTables<float> df{};
