@@ -289,7 +289,8 @@ template <typename T, int MODE>
 int launch_mode(int lds_bytes, int64_t nunits, DirArgs<T>& ar, void* stream) {
     const void* kern = (const void*)direct_kernel<T, MODE>;
     if (lds_bytes > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        // (always the same limit: threads that launch different lists cannot lower it for each other)
+        const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
         if (e != hipSuccess) return (int)e;
     }
     return dir_launches(nunits, 8LL * ar.chunk, kDirThreads, [&](int64_t first, unsigned grid) {

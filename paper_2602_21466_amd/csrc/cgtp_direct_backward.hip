@@ -340,9 +340,9 @@ int launch_direct_backward(const DgTables& tb, const float* x1, const float* x2,
             lds = std::max(lds, ls.lds_bytes[c]);
         }
         if (ar.wg0[ar.ncls] == 0) continue;
-        if (lds > 64 * 1024) {
+        if (lds > 64 * 1024) {   // (always the same limit, as for the forward)
             const hipError_t e = hipFuncSetAttribute((const void*)direct_backward_kernel,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
             if (e != hipSuccess) return (int)e;
         }
         const int err = dir_launches(ar.wg0[ar.ncls], 8, kDgThreads, [&](int64_t first, unsigned grid) {

@@ -136,6 +136,41 @@ def test_outputs_do_not_depend_on_the_number_of_pairs(L, N, dtype):
 
 
 @pytest.mark.gpu
+def test_threads_share_a_plan():
+    """One plan, two threads on streams of their own: few pairs (short list) and many (long list), which take
+    different amounts of LDS above 64 KiB in fp64."""
+    import threading
+    import torch
+    import paper_2602_21466_amd as lib
+    L, N = 12, 400
+    plan = lib.Plan(L, dtype="fp64")
+    x1, x2 = _rows(torch, N, (L + 1) ** 2, "fp64", 1).cuda(), _rows(torch, N, (L + 1) ** 2, "fp64", 2).cuda()
+    ref = plan.forward(x1, x2)
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(n):
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                z = torch.empty(n, (L + 1) ** 4, dtype=torch.float64, device="cuda")
+                for _ in range(40):
+                    plan.forward(x1[:n], x2[:n], z, stream=s)
+                s.synchronize()
+                if not torch.equal(z, ref[:n]):
+                    wrong.append(n)
+        except Exception as e:
+            wrong.append(e)
+    threads = [threading.Thread(target=work, args=(n,)) for n in (3, N, 17, N)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong
+    plan.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shared,weights", [(True, "channel"), (False, "pair"), (True, "none")])
 def test_routes_agree(shared, weights):
     """The direct contraction and the sphere-grid kernels (explicit grid): plain, real, channels (bound: the sum of
